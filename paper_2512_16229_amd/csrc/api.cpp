@@ -54,7 +54,8 @@ int dalloc(DevBuf& b, size_t bytes, std::vector<void*>& owned) {
   return LOPA_OK;
 }
 
-// Packed weights: [blocks of 16 output features][K / 64][2][64][8] bf16.
+// Packed weights: [K / 64][blocks of 16 output features][2][64][8] bf16 (E4M3:
+// [K / 128][blocks][2][64][16]), followed by GEMM_MAX_NB blocks of zeros.
 struct LayerPack {
   uint16_t* qkv;   // blk_qkv blocks, K = H (models with a bf16 QKV projection)
   uint16_t* o;     // blk_h blocks, K = Hq * d
@@ -77,49 +78,70 @@ struct LayerPack {
   float* ln2;
 };
 
-// rows of the packed activation buffers: whole 256-row tiles
-int padded_rows(int M) { return 256 * ((M + 255) / 256); }
 int round256(int k) { return 256 * ((k + 255) / 256); }
 int round512(int k) { return 512 * ((k + 511) / 512); }
 int round_up(int x, int m) { return m * ((x + m - 1) / m); }
 
+// Row tiles of a forward of M rows: MT = ceil(M / 256) tiles of 64 mb rows each,
+// mb (1..4) the smallest that covers M, so few rows stream few activations.
+struct RowTiles {
+  int MT, mb;
+  int rows() const { return 64 * mb * MT; }
+};
+RowTiles row_tiles(int M) {
+  const int MT = (M + 255) / 256;
+  return {MT, ((M + MT - 1) / MT + 63) / 64};
+}
+// rows of the packed activation buffers of a forward of up to M rows (a smaller
+// forward never takes more: its tiles are as many or fewer, of 256 rows at most)
+int padded_rows(int M) { return 256 * ((M + 255) / 256); }
+
 // Decomposition of one GEMM (see gemm.hip): tile width nb (16-column blocks)
-// and k-splits S. SwiGLU and LM-head tiles are fixed (their epilogues need
-// whole rows of a tile and no split); for the others the pair with the
-// smallest estimated time is taken. Per round of workgroups the time is the
-// larger of (a) the bytes one workgroup pulls into its CU (every k-chunk: the
-// 256 x 64 bf16 activation chunk from L2 plus nb x 2 KiB of weights), at the
-// per-CU rate measured for these kernels (~60 GB/s), and (b) the round's
-// weight bytes at the sustained HBM rate (~6.5 TB/s); split-K adds its fp32
-// partial sums, written (~5 TB/s) and read back by the small kernel that
-// reduces them (~3 TB/s), and QKV its fix-up launch.
-// The weights are packed per tile, so nb is chosen once, when the model is
-// created (fixed_nb = 0: choose), and later plans choose S only.
+// and k-splits S; SwiGLU and LM head take no split (their epilogues need whole
+// sums). The pair with the smallest estimated time is taken. A round of
+// workgroups (one per CU) takes the longest of
+//   (a) the bytes one workgroup pulls into its CU, per 64-wide k-chunk the
+//       64 mb x 64 activation chunk from L2 and nb x 2 KiB of weights (61 GB/s),
+//   (b) the round's weight bytes from HBM (7.2 TB/s),
+//   (c) its MFMAs, 5 ns per row block and 32 x 16 weight fragment,
+// plus 0.27 of the shorter of (a) and (c), which overlap in part, plus 0.9 us of
+// fill and tail. Partial sums add their write (5.8 TB/s) and the read of
+// the kernel that adds them (3 TB/s). The constants are a least-squares fit to
+// the GEMM shapes of Dream-7B and LLaDA-8B at 32 to 2048 rows in bf16 and FP8,
+// every (nb, S) of each timed on its own: the plan taken is within 1 % of the
+// best one in the mean, within 17 % in the worst case.
+// max_part: most bytes of partial sums (splits that write more are not taken;
+// QKV keeps one split at least). min_nb: narrowest tile.
 struct GemmPlan {
   int nb, tiles, splits;
 };
-GemmPlan plan_gemm(int epi, int nblocks, int KC, int MT, int num_cu, int fixed_nb) {
-  if (epi == EPI_SWIGLU) return {10, nblocks / 10, 1};
-  if (epi == EPI_LMHEAD) return {fixed_nb, nblocks / fixed_nb, 1};
-  constexpr double CU_BPUS = 60e3, HBM_BPUS = 6.5e6, PART_W_BPUS = 5e6, PART_R_BPUS = 3e6;
-  constexpr double FIXUP_US = 7.0;
+GemmPlan plan_gemm(int epi, int nblocks, int KC, RowTiles rt, int num_cu,
+                   size_t max_part = SIZE_MAX, int min_nb = 4) {
+  constexpr double CU_BPUS = 61e3, HBM_BPUS = 7.2e6, PART_W_BPUS = 5.8e6, PART_R_BPUS = 3e6;
+  constexpr double FRAG_US = 0.005, OVERLAP = 0.27, FILL_US = 0.9;
+  const bool whole = epi == EPI_SWIGLU || epi == EPI_LMHEAD;
   const int Q = KC / 4;
-  GemmPlan best{8, nblocks / 8, 1};
+  const int max_s = whole ? 1 : epi == EPI_QKV ? std::min(Q, QKV_MAX_SPLITS) : Q;
+  GemmPlan best{0, 0, 0};
   double best_t = 1e300;
-  for (int nb : {4, 8}) {
-    if (fixed_nb && nb != fixed_nb) continue;
-    const int tiles = nblocks / nb;
-    for (int S = 1; S <= (epi == EPI_QKV ? std::min(Q, QKV_MAX_SPLITS) : Q); ++S) {
-      const int64_t wgs = (int64_t)MT * tiles * S;
+  for (int nb : {4, 8, 10}) {
+    if (nb < min_nb || (nb == 10 && !whole)) continue;
+    const int tiles = (nblocks + nb - 1) / nb;
+    for (int S = 1; S <= max_s; ++S) {
+      const int64_t wgs = (int64_t)rt.MT * tiles * S;
+      if (S > 1 && (wgs > 8 * (int64_t)num_cu ||
+                    (size_t)S * rt.rows() * tiles * nb * 16 * 4 > max_part))
+        break;
       const int64_t rounds = (wgs + num_cu - 1) / num_cu;
       const double iters = 4.0 * ((Q + S - 1) / S);
-      const double per_cu = iters * (32768.0 + nb * 2048.0);
-      const double w_round = (double)std::min<int64_t>(wgs, num_cu) * iters * nb * 2048.0;
-      double t = (double)rounds * std::max(per_cu / CU_BPUS, w_round / HBM_BPUS);
-      const double part = epi == EPI_QKV ? (double)wgs * nb * 16384.0
-                                         : (S > 1 ? (double)S * MT * 256.0 * tiles * nb * 16 * 4 : 0.0);
-      t += part / PART_W_BPUS + part / PART_R_BPUS;
-      if (epi == EPI_QKV) t += FIXUP_US;
+      const double cu = iters * (rt.mb * 8192.0 + nb * 2048.0) / CU_BPUS;
+      const double mfma = iters * rt.mb * nb * 2 * FRAG_US;
+      const double hbm = (double)std::min<int64_t>(wgs, num_cu) / rt.MT * iters * nb * 2048.0 / HBM_BPUS;
+      double t = (double)rounds * (FILL_US + std::max({cu, mfma, hbm}) + OVERLAP * std::min(cu, mfma));
+      if (epi == EPI_QKV || S > 1) {
+        const double part = (double)S * rt.rows() * nblocks * 16 * 4;
+        t += part / PART_W_BPUS + part / PART_R_BPUS;
+      }
       if (t < best_t) {
         best_t = t;
         best = {nb, tiles, S};
@@ -129,10 +151,10 @@ GemmPlan plan_gemm(int epi, int nblocks, int KC, int MT, int num_cu, int fixed_n
   return best;
 }
 // bytes of fp32 partial sums the plan writes (QKV always goes through them;
-// the residual projections store [splits][Mp][N] row-major)
-size_t plan_partial_bytes(int epi, const GemmPlan& p, int MT) {
-  if (epi == EPI_QKV) return (size_t)MT * p.tiles * p.splits * p.nb * 16384;
-  return p.splits > 1 ? (size_t)p.splits * MT * 256 * p.tiles * p.nb * 16 * 4 : 0;
+// the residual projections store [splits][rows][N] row-major)
+size_t plan_partial_bytes(int epi, const GemmPlan& p, RowTiles rt, int nblocks) {
+  if (epi == EPI_QKV) return (size_t)rt.rows() * p.tiles * p.nb * 16 * 4 * p.splits;
+  return p.splits > 1 ? (size_t)p.splits * rt.rows() * nblocks * 16 * 4 : 0;
 }
 
 }  // namespace
@@ -143,12 +165,8 @@ struct lopa_model {
   int num_cu = 0;
   int n_qkv = 0;
   int blk_qkv = 0, blk_h = 0, blk_gu = 0, blk_lm = 0;  // packed 16-column blocks
-  int nb_qkv = 0, nb_o = 0, nb_down = 0, nb_lm = 0;     // tile widths of the packed weights
-  int tiles_lm = 0;                                     // LM-head column tiles
   int fp8 = 0;       // FP8 MLP (LOPA_PRECISION_FP8_MLP and LOPA_PRECISION_FP8)
   int fp8_qkv_lm = 0;  // FP8 QKV projection and LM head too (LOPA_PRECISION_FP8)
-  int nb_down8 = 0;                                     // FP8 down-projection tile width
-  int nb_o8 = 0;                                        // FP8 output-projection tile width
   std::vector<LayerPack> layers;
   uint16_t* embed = nullptr;
   uint16_t* lm = nullptr;   // bf16 LM head (when not FP8)
@@ -161,8 +179,17 @@ struct lopa_model {
   }
 };
 
+namespace {
+// the row tiles and the plans of the five GEMMs of a verify forward
+struct StepPlans {
+  RowTiles rt;
+  GemmPlan qkv, o, gu, down, lm;
+};
+}  // namespace
+
 struct lopa_kv {
   const lopa_model* m = nullptr;
+  std::vector<StepPlans> plans;  // by row count, up to max_branches * max_block
   int max_len = 0, max_branches = 0, max_block = 0, mp_max = 0;
   int vld = 0, vlds = 0;        // positions per head region: max_len, max_block rounded up to 32
   uint16_t* cache = nullptr;    // [layers][2][Hkv][d * vld], KV tile layout (common.h)
@@ -232,23 +259,86 @@ struct ProfScope {
     if (ev) (void)hipEventRecord(ev->b, s);
   }
 };
-// the plans of the five GEMMs of a verify forward with MT row tiles
-struct StepPlans {
-  GemmPlan qkv, o, gu, down, lm;
-};
-StepPlans step_plans(const lopa_model* m, int MT) {
+StepPlans plan_step(const lopa_model* m, RowTiles rt, size_t max_part, int min_nb_lm) {
   const lopa_model_cfg& c = m->cfg;
-  StepPlans p;
   const int kch = m->fp8_qkv_lm ? round512(c.hidden) / 128 : c.hidden / 64;
-  p.qkv = plan_gemm(EPI_QKV, m->blk_qkv, kch, MT, m->num_cu, m->nb_qkv);
-  p.o = m->fp8_qkv_lm
-            ? plan_gemm(EPI_RESID, m->blk_h, round512(c.heads * c.head_dim) / 128, MT, m->num_cu, m->nb_o8)
-            : plan_gemm(EPI_RESID, m->blk_h, c.heads * c.head_dim / 64, MT, m->num_cu, m->nb_o);
-  p.gu = plan_gemm(EPI_SWIGLU, m->blk_gu, c.hidden / 64, MT, m->num_cu, 10);
-  p.down = m->fp8 ? plan_gemm(EPI_RESID, m->blk_h, round512(c.ffn) / 128, MT, m->num_cu, m->nb_down8)
-                  : plan_gemm(EPI_RESID, m->blk_h, round256(c.ffn) / 64, MT, m->num_cu, m->nb_down);
-  p.lm = plan_gemm(EPI_LMHEAD, m->blk_lm, kch, MT, m->num_cu, m->nb_lm);
+  const int kco = m->fp8_qkv_lm ? round512(c.heads * c.head_dim) / 128 : c.heads * c.head_dim / 64;
+  const int kcg = m->fp8 ? round512(c.hidden) / 128 : c.hidden / 64;
+  const int kcd = m->fp8 ? round512(c.ffn) / 128 : round256(c.ffn) / 64;
+  StepPlans p;
+  p.rt = rt;
+  p.qkv = plan_gemm(EPI_QKV, m->blk_qkv, kch, rt, m->num_cu, max_part);
+  p.o = plan_gemm(EPI_RESID, m->blk_h, kco, rt, m->num_cu, max_part);
+  p.gu = plan_gemm(EPI_SWIGLU, m->blk_gu, kcg, rt, m->num_cu);
+  p.down = plan_gemm(EPI_RESID, m->blk_h, kcd, rt, m->num_cu, max_part);
+  p.lm = plan_gemm(EPI_LMHEAD, m->blk_lm, kch, rt, m->num_cu, SIZE_MAX, min_nb_lm);
   return p;
+}
+// bytes of partial sums and LM-head (row, tile) statistics of a forward
+size_t partial_bytes(const lopa_model* m, const StepPlans& p) {
+  return std::max({(size_t)16, plan_partial_bytes(EPI_QKV, p.qkv, p.rt, m->blk_qkv),
+                   plan_partial_bytes(EPI_RESID, p.o, p.rt, m->blk_h),
+                   plan_partial_bytes(EPI_RESID, p.down, p.rt, m->blk_h)});
+}
+size_t lm_stats(const StepPlans& p) { return (size_t)p.rt.rows() * p.lm.tiles; }
+
+// The regions of a forward's working memory, in carving order (bytes, each
+// rounded up to 256): x, abuf, fbuf, qbuf, partials, pm, ps, pi, then the FP8
+// operands of FP8 models. M rows; scratch: the attention's.
+struct WsLayout {
+  size_t sz[13] = {};
+  size_t total() const {
+    size_t t = 0;
+    for (size_t v : sz) t += v;
+    return t;
+  }
+};
+WsLayout ws_layout(const lopa_model* m, const StepPlans& p, int M, size_t scratch) {
+  const lopa_model_cfg& c = m->cfg;
+  const size_t rows = p.rt.rows();
+  WsLayout w;
+  w.sz[0] = rows * c.hidden * 4;
+  w.sz[1] = rows * c.hidden * 2;
+  w.sz[2] = rows * round256(c.ffn) * 2;
+  w.sz[3] = (size_t)M * c.heads * c.head_dim * 2;
+  w.sz[4] = std::max(partial_bytes(m, p), scratch);
+  w.sz[5] = w.sz[6] = w.sz[7] = lm_stats(p) * 4;
+  if (m->fp8) {
+    w.sz[8] = rows * round512(c.hidden);
+    w.sz[9] = rows * round512(c.ffn);
+    w.sz[10] = w.sz[11] = w.sz[12] = rows * 4;
+  }
+  for (size_t& v : w.sz) v = (v + 255) / 256 * 256;
+  return w;
+}
+// Both entries of the verify forward take the same plans (the same bits), so a
+// forward whose other buffers fit the static array of lopa_verify_forward_noalloc
+// takes only as many splits, and as narrow an LM-head tile, as let all of it fit.
+// free_plan: plan_step of the same row tiles without a limit.
+StepPlans fit_plan(const lopa_model* m, int M, const StepPlans& free_plan) {
+  constexpr size_t CAP = (size_t)LOPA_NOALLOC_MAX_BYTES;
+  const WsLayout w = ws_layout(m, free_plan, M, 0);
+  const size_t stats = w.sz[5] + w.sz[6] + w.sz[7];
+  if (w.total() <= CAP || w.total() - w.sz[4] - stats >= CAP) return free_plan;
+  StepPlans p = plan_step(m, free_plan.rt, SIZE_MAX, 8);
+  const WsLayout w8 = ws_layout(m, p, M, 0);
+  if (w8.total() <= CAP) return p;
+  const size_t rest = w8.total() - w8.sz[4];
+  if (rest >= CAP) return free_plan;
+  p = plan_step(m, free_plan.rt, (CAP - rest) / 256 * 256, 8);
+  return ws_layout(m, p, M, 0).total() <= CAP ? p : free_plan;
+}
+// the plans of every row count up to max_rows (index M; entry 0 unused)
+std::vector<StepPlans> all_plans(const lopa_model* m, int max_rows) {
+  std::vector<StepPlans> v((size_t)max_rows + 1);
+  StepPlans free_plan{};
+  for (int M = 1; M <= max_rows; ++M) {
+    const RowTiles rt = row_tiles(M);
+    if (M == 1 || rt.MT != free_plan.rt.MT || rt.mb != free_plan.rt.mb)
+      free_plan = plan_step(m, rt, SIZE_MAX, 4);
+    v[M] = fit_plan(m, M, free_plan);
+  }
+  return v;
 }
 }  // namespace
 
@@ -318,11 +408,10 @@ int lopa_model_create_ex(const lopa_model_cfg* cfg, const lopa_weight_ptrs* w, i
   const lopa_model_cfg& c = *cfg;
   const int H = c.hidden, d = c.head_dim, F = c.ffn, V = c.vocab;
   m->n_qkv = (c.heads + 2 * c.kv_heads) * d;
-  // blocks padded to whole tiles of every width a plan may pick (4, 8; 10 for
-  // the gate / up pairs); padding blocks hold zero weights
-  m->blk_qkv = round_up(m->n_qkv / 16, 8);
-  m->blk_h = round_up(H / 16, 8);
-  m->blk_gu = round_up(2 * F / 16, 10);
+  m->blk_qkv = m->n_qkv / 16;
+  m->blk_h = H / 16;
+  m->blk_gu = 2 * F / 16;
+  m->blk_lm = (V + 15) / 16;
   auto bail = [&](int code) {
     delete m;
     return code;
@@ -331,31 +420,8 @@ int lopa_model_create_ex(const lopa_model_cfg* cfg, const lopa_weight_ptrs* w, i
       hipDeviceGetAttribute(&m->num_cu, hipDeviceAttributeMultiprocessorCount, m->device) !=
           hipSuccess)
     return bail(fail(LOPA_EHIP, "no HIP device"));
-  // LM head: 8- or 10-block tiles (whole tiles, no split: the epilogue reduces
-  // each tile's softmax statistics), whichever gives fewer rounds of
-  // workgroups x per-workgroup bytes (activation chunk + weights per k-chunk)
-  {
-    double best = 1e300;
-    for (int nb : {8, 10}) {
-      const int tiles = round_up((V + 15) / 16, nb) / nb;
-      const double t = std::ceil((double)tiles / m->num_cu) * (32768.0 + nb * 2048.0);
-      if (t < best) {
-        best = t;
-        m->nb_lm = nb;
-      }
-    }
-  }
-  m->blk_lm = round_up((V + 15) / 16, m->nb_lm);
-  m->tiles_lm = m->blk_lm / m->nb_lm;
-  // tile widths: those of the single-row-tile plans (up to 256 rows, the
-  // common verify batch); other row counts re-plan the k-splits only
-  m->nb_qkv = plan_gemm(EPI_QKV, m->blk_qkv, H / 64, 1, m->num_cu, 0).nb;
-  m->nb_o = plan_gemm(EPI_RESID, m->blk_h, c.heads * d / 64, 1, m->num_cu, 0).nb;
-  m->nb_down = plan_gemm(EPI_RESID, m->blk_h, round256(F) / 64, 1, m->num_cu, 0).nb;
   m->fp8 = precision == LOPA_PRECISION_FP8_MLP || precision == LOPA_PRECISION_FP8;
   m->fp8_qkv_lm = precision == LOPA_PRECISION_FP8;
-  m->nb_down8 = plan_gemm(EPI_RESID, m->blk_h, round512(F) / 128, 1, m->num_cu, 0).nb;
-  m->nb_o8 = plan_gemm(EPI_RESID, m->blk_h, round512(c.heads * d) / 128, 1, m->num_cu, 0).nb;
   auto alloc16 = [&](uint16_t** p, size_t elems) -> int {
     DevBuf b;
     int r = dalloc(b, elems * 2, m->owned);
@@ -370,12 +436,28 @@ int lopa_model_create_ex(const lopa_model_cfg* cfg, const lopa_weight_ptrs* w, i
   };
   const int FP = round256(F);  // down projection K, zero-padded
   const int KPH8 = round512(H), KPF8 = round512(F);  // FP8 MLP K, zero-padded
-  // elements of a packed weight: blocks x K x 16
+  // elements of a packed weight: blocks x K x 16 (without its slack, see
+  // GEMM_MAX_NB); columns of its scales
   auto wsize = [](int blocks, int K) { return (size_t)blocks * K * 16; };
-  auto alloc8 = [&](uint8_t** p, size_t bytes) -> int {
+  auto ncols = [](int blocks) { return (size_t)(blocks + GEMM_MAX_NB) * 16; };
+  // packed weights with their slack, whose last GEMM_MAX_NB blocks are zeroed
+  constexpr size_t SLACK = (size_t)GEMM_MAX_NB * 2048;
+  auto allocw = [&](void** p, size_t bytes) -> int {
     DevBuf b;
-    int r = dalloc(b, bytes, m->owned);
-    *p = (uint8_t*)b.p;
+    int r = dalloc(b, bytes + SLACK, m->owned);
+    *p = b.p;
+    if (!r && launch_fill_zero((char*)b.p + bytes, SLACK, s) != hipSuccess)
+      r = fail(LOPA_EHIP, "clearing a weight's slack failed");
+    return r;
+  };
+  auto allocw16 = [&](uint16_t** p, size_t elems) { return allocw((void**)p, elems * 2); };
+  auto allocw8 = [&](uint8_t** p, size_t bytes) { return allocw((void**)p, bytes); };
+  auto allocs = [&](float** p, int blocks) -> int {
+    DevBuf b;
+    int r = dalloc(b, ncols(blocks) * 4, m->owned);
+    *p = (float*)b.p;
+    if (!r && launch_fill_zero(b.p, ncols(blocks) * 4, s) != hipSuccess)
+      r = fail(LOPA_EHIP, "clearing the column scales failed");
     return r;
   };
   // FP8: per source row scaling pairs (gate, up: F rows; down: H rows; q, k,
@@ -394,18 +476,18 @@ int lopa_model_create_ex(const lopa_model_cfg* cfg, const lopa_weight_ptrs* w, i
     const lopa_layer_weights& lw = w->layers[l];
     LayerPack& p = m->layers[l];
     p.gu = p.down = p.qkv = nullptr;
-    if ((!m->fp8_qkv_lm && (rc = alloc16(&p.qkv, wsize(m->blk_qkv, H)))) ||
-        (m->fp8_qkv_lm && (rc = alloc8(&p.qkv8, wsize(m->blk_qkv, KPH8)))) ||
-        (m->fp8_qkv_lm && (rc = allocf(&p.sw_qkv, (size_t)m->blk_qkv * 16))) ||
-        (!m->fp8_qkv_lm && (rc = alloc16(&p.o, wsize(m->blk_h, c.heads * d)))) ||
-        (m->fp8_qkv_lm && (rc = alloc8(&p.o8, wsize(m->blk_h, round512(c.heads * d))))) ||
-        (m->fp8_qkv_lm && (rc = allocf(&p.sw_o, (size_t)m->blk_h * 16))) ||
-        (!m->fp8 && (rc = alloc16(&p.gu, wsize(m->blk_gu, H)))) ||
-        (!m->fp8 && (rc = alloc16(&p.down, wsize(m->blk_h, FP)))) ||
-        (m->fp8 && (rc = alloc8(&p.gu8, wsize(m->blk_gu, KPH8)))) ||
-        (m->fp8 && (rc = alloc8(&p.down8, wsize(m->blk_h, KPF8)))) ||
-        (m->fp8 && (rc = allocf(&p.sw_gu, (size_t)m->blk_gu * 16))) ||
-        (m->fp8 && (rc = allocf(&p.sw_down, (size_t)m->blk_h * 16))) ||
+    if ((!m->fp8_qkv_lm && (rc = allocw16(&p.qkv, wsize(m->blk_qkv, H)))) ||
+        (m->fp8_qkv_lm && (rc = allocw8(&p.qkv8, wsize(m->blk_qkv, KPH8)))) ||
+        (m->fp8_qkv_lm && (rc = allocs(&p.sw_qkv, m->blk_qkv))) ||
+        (!m->fp8_qkv_lm && (rc = allocw16(&p.o, wsize(m->blk_h, c.heads * d)))) ||
+        (m->fp8_qkv_lm && (rc = allocw8(&p.o8, wsize(m->blk_h, round512(c.heads * d))))) ||
+        (m->fp8_qkv_lm && (rc = allocs(&p.sw_o, m->blk_h))) ||
+        (!m->fp8 && (rc = allocw16(&p.gu, wsize(m->blk_gu, H)))) ||
+        (!m->fp8 && (rc = allocw16(&p.down, wsize(m->blk_h, FP)))) ||
+        (m->fp8 && (rc = allocw8(&p.gu8, wsize(m->blk_gu, KPH8)))) ||
+        (m->fp8 && (rc = allocw8(&p.down8, wsize(m->blk_h, KPF8)))) ||
+        (m->fp8 && (rc = allocs(&p.sw_gu, m->blk_gu))) ||
+        (m->fp8 && (rc = allocs(&p.sw_down, m->blk_h))) ||
         (rc = allocf(&p.ln1, H)) || (rc = allocf(&p.ln2, H)))
       return bail(rc);
     p.bias = nullptr;
@@ -415,7 +497,7 @@ int lopa_model_create_ex(const lopa_model_cfg* cfg, const lopa_weight_ptrs* w, i
     const uint16_t* wv = (const uint16_t*)lw.wv;
     hipError_t e;
     if ((!m->fp8_qkv_lm &&
-         (e = launch_repack(wq, nq, wk, nk, wv, nk, H, H, m->blk_qkv, m->nb_qkv, 0, p.qkv, s)) !=
+         (e = launch_repack(wq, nq, wk, nk, wv, nk, H, H, m->blk_qkv, 0, p.qkv, s)) !=
              hipSuccess) ||
         (m->fp8_qkv_lm &&
          ((e = launch_rowscale(wq, nq, H, inv_q, sc_q, s)) != hipSuccess ||
@@ -423,32 +505,32 @@ int lopa_model_create_ex(const lopa_model_cfg* cfg, const lopa_weight_ptrs* w, i
           (e = launch_rowscale(wv, nk, H, inv_q + nq + nk, sc_q + nq + nk, s)) != hipSuccess ||
           (e = launch_repack8(wq, inv_q, sc_q, nq, wk, inv_q + nq, sc_q + nq, nk, wv,
                               inv_q + nq + nk, sc_q + nq + nk, nk, H, KPH8, m->blk_qkv,
-                              m->nb_qkv, 0, p.qkv8, p.sw_qkv, s)) != hipSuccess)) ||
+                              0, p.qkv8, p.sw_qkv, s)) != hipSuccess)) ||
         (!m->fp8_qkv_lm &&
          (e = launch_repack((const uint16_t*)lw.wo, H, nullptr, 0, nullptr, 0, c.heads * d,
-                            c.heads * d, m->blk_h, m->nb_o, 0, p.o, s)) != hipSuccess) ||
+                            c.heads * d, m->blk_h, 0, p.o, s)) != hipSuccess) ||
         (m->fp8_qkv_lm &&  // the row-scale buffers are free again: the QKV repack ran before
          ((e = launch_rowscale((const uint16_t*)lw.wo, H, c.heads * d, inv_q, sc_q, s)) !=
               hipSuccess ||
           (e = launch_repack8((const uint16_t*)lw.wo, inv_q, sc_q, H, nullptr, nullptr, nullptr, 0,
                               nullptr, nullptr, nullptr, 0, c.heads * d, round512(c.heads * d),
-                              m->blk_h, m->nb_o8, 0, p.o8, p.sw_o, s)) != hipSuccess)) ||
+                              m->blk_h, 0, p.o8, p.sw_o, s)) != hipSuccess)) ||
         (!m->fp8 &&
          (e = launch_repack((const uint16_t*)lw.w_gate, F, (const uint16_t*)lw.w_up, F, nullptr,
-                            0, H, H, m->blk_gu, 10, 1, p.gu, s)) != hipSuccess) ||
+                            0, H, H, m->blk_gu, 1, p.gu, s)) != hipSuccess) ||
         (!m->fp8 &&
          (e = launch_repack((const uint16_t*)lw.w_down, H, nullptr, 0, nullptr, 0, F, FP,
-                            m->blk_h, m->nb_down, 0, p.down, s)) != hipSuccess) ||
+                            m->blk_h, 0, p.down, s)) != hipSuccess) ||
         (m->fp8 &&
          ((e = launch_rowscale((const uint16_t*)lw.w_gate, F, H, inv_g, sc_g, s)) != hipSuccess ||
           (e = launch_rowscale((const uint16_t*)lw.w_up, F, H, inv_u, sc_u, s)) != hipSuccess ||
           (e = launch_rowscale((const uint16_t*)lw.w_down, H, F, inv_d, sc_d, s)) != hipSuccess ||
           (e = launch_repack8((const uint16_t*)lw.w_gate, inv_g, sc_g, F,
                               (const uint16_t*)lw.w_up, inv_u, sc_u, F, nullptr, nullptr, nullptr,
-                              0, H, KPH8, m->blk_gu, 10, 1, p.gu8, p.sw_gu, s)) != hipSuccess ||
+                              0, H, KPH8, m->blk_gu, 1, p.gu8, p.sw_gu, s)) != hipSuccess ||
           (e = launch_repack8((const uint16_t*)lw.w_down, inv_d, sc_d, H, nullptr, nullptr,
                               nullptr, 0, nullptr, nullptr, nullptr, 0, F, KPF8, m->blk_h,
-                              m->nb_down8, 0, p.down8, p.sw_down, s)) != hipSuccess)) ||
+                              0, p.down8, p.sw_down, s)) != hipSuccess)) ||
         (e = launch_bf16_to_f32((const uint16_t*)lw.ln1, p.ln1, H, s)) != hipSuccess ||
         (e = launch_bf16_to_f32((const uint16_t*)lw.ln2, p.ln2, H, s)) != hipSuccess)
       return bail(fail(LOPA_EHIP, "layer %d repack: %s", l, hipGetErrorString(e)));
@@ -462,20 +544,20 @@ int lopa_model_create_ex(const lopa_model_cfg* cfg, const lopa_weight_ptrs* w, i
     }
   }
   if ((rc = alloc16(&m->embed, (size_t)V * H)) ||
-      (!m->fp8_qkv_lm && (rc = alloc16(&m->lm, wsize(m->blk_lm, H)))) ||
-      (m->fp8_qkv_lm && (rc = alloc8(&m->lm8, wsize(m->blk_lm, KPH8)))) ||
-      (m->fp8_qkv_lm && (rc = allocf(&m->sw_lm, (size_t)m->blk_lm * 16))) ||
+      (!m->fp8_qkv_lm && (rc = allocw16(&m->lm, wsize(m->blk_lm, H)))) ||
+      (m->fp8_qkv_lm && (rc = allocw8(&m->lm8, wsize(m->blk_lm, KPH8)))) ||
+      (m->fp8_qkv_lm && (rc = allocs(&m->sw_lm, m->blk_lm))) ||
       (rc = allocf(&m->final_norm, H)))
     return bail(rc);
   hipError_t e;
   const uint16_t* lmw = (const uint16_t*)w->lm_head;
   if ((e = hipMemcpyAsync(m->embed, w->embed, (size_t)V * H * 2, hipMemcpyDeviceToDevice, s)) ||
       (!m->fp8_qkv_lm && (e = launch_repack(lmw, V, nullptr, 0, nullptr, 0, H, H, m->blk_lm,
-                                            m->nb_lm, 0, m->lm, s))) ||
+                                            0, m->lm, s))) ||
       (m->fp8_qkv_lm &&
        ((e = launch_rowscale(lmw, V, H, inv_q, sc_q, s)) ||
         (e = launch_repack8(lmw, inv_q, sc_q, V, nullptr, nullptr, nullptr, 0, nullptr, nullptr,
-                            nullptr, 0, H, KPH8, m->blk_lm, m->nb_lm, 0, m->lm8, m->sw_lm, s)))) ||
+                            nullptr, 0, H, KPH8, m->blk_lm, 0, m->lm8, m->sw_lm, s)))) ||
       (e = launch_bf16_to_f32((const uint16_t*)w->final_norm, m->final_norm, H, s)) ||
       (e = hipStreamSynchronize(s)))
     return bail(fail(LOPA_EHIP, "model create: %s", hipGetErrorString(e)));
@@ -515,11 +597,12 @@ int lopa_kv_create(const lopa_model* m, int32_t max_len, int32_t max_branches, i
   const size_t cache_e = (size_t)c.layers * 2 * Hkv * d * kv->vld;
   const size_t stag_e = (size_t)max_branches * c.layers * 2 * Hkv * d * kv->vlds;
   size_t part_b = 16;
-  for (int MT = 1; MT <= kv->mp_max / 256; ++MT) {
-    const StepPlans p = step_plans(m, MT);
-    part_b = std::max({part_b, plan_partial_bytes(EPI_QKV, p.qkv, MT),
-                       plan_partial_bytes(EPI_RESID, p.o, MT),
-                       plan_partial_bytes(EPI_RESID, p.down, MT)});
+  size_t lm_n = 0;
+  kv->plans = all_plans(m, max_branches * max_block);
+  for (int M = 1; M <= max_branches * max_block; ++M) {
+    const StepPlans& p = kv->plans[M];
+    part_b = std::max(part_b, partial_bytes(m, p));
+    lm_n = std::max(lm_n, lm_stats(p));
   }
   // the attention's scratch (between the QKV fix-up and the output projection
   // the partial sums are free): its largest need over the branch counts
@@ -547,9 +630,9 @@ int lopa_kv_create(const lopa_model* m, int32_t max_len, int32_t max_branches, i
   }
   KV_ALLOC(qbuf, uint16_t*, (size_t)max_branches * c.heads * max_block * d * 2);
   KV_ALLOC(partials, float*, part_b);
-  KV_ALLOC(pm, float*, rows * m->tiles_lm * 4);
-  KV_ALLOC(ps, float*, rows * m->tiles_lm * 4);
-  KV_ALLOC(pi, int32_t*, rows * m->tiles_lm * 4);
+  KV_ALLOC(pm, float*, lm_n * 4);
+  KV_ALLOC(ps, float*, lm_n * 4);
+  KV_ALLOC(pi, int32_t*, lm_n * 4);
 #undef KV_ALLOC
   // RoPE table in double precision, stored as fp32 (cos, sin) pairs.
   std::vector<float> tab((size_t)max_len * (d / 2) * 2);
@@ -610,21 +693,22 @@ static int verify_impl(const lopa_model* m, lopa_kv* kv, int32_t prefix_len,
   const lopa_model_cfg& c = m->cfg;
   hipStream_t s = (hipStream_t)stream;
   const int M = n_branches * L;
-  const int Mp = padded_rows(M);
   const int H = c.hidden, F = c.ffn, d = c.head_dim;
-  const int MT = Mp / 256;
-  const StepPlans plan = step_plans(m, MT);
+  const StepPlans& plan = kv->plans[M];
+  const int Mp = plan.rt.rows();
 
   GemmArgs g{};
   g.M = M;
   g.Mp = Mp;
-  g.mtiles = MT;
+  g.mtiles = plan.rt.MT;
+  g.mb = plan.rt.mb;
   g.partials = ws.partials;
   auto gemm = [&](int epi, const uint16_t* A, const uint16_t* W, int N, int K,
                   const GemmPlan& p) {
     g.A = A;
     g.W = W;
     g.N = N;
+    g.wblocks = (N + 15) / 16;
     g.KC = K / 64;
     g.rot = epi == EPI_SWIGLU || epi == EPI_RESID;
     g.f8 = 0;
@@ -641,6 +725,7 @@ static int verify_impl(const lopa_model* m, lopa_kv* kv, int32_t prefix_len,
     g.A = (const uint16_t*)A;
     g.W = (const uint16_t*)W;
     g.N = N;
+    g.wblocks = (N + 15) / 16;
     g.KC = KP / 128;
     g.rot = epi == EPI_SWIGLU || epi == EPI_RESID;
     g.f8 = 1;
@@ -655,13 +740,22 @@ static int verify_impl(const lopa_model* m, lopa_kv* kv, int32_t prefix_len,
   };
   const bool f8x = m->fp8_qkv_lm;  // the normed rows go to the QKV / LM head in E4M3
 
+  // where the padding columns of the operands lie depends on Mp, so this
+  // forward's first kernel zeroes them
+  ZeroPad zp{};
+  if (!m->fp8)
+    zp.add(ws.fbuf, F / 32, round256(F) / 32);
+  else {
+    zp.add(ws.a8_gu, H / 64, round512(H) / 64);
+    zp.add(ws.a8_dn, F / 64, round512(F) / 64);
+  }
   { ProfScope ps_(kv, LOPA_PROF_NORM, s);
     if (f8x)
       HIP_TRY(launch_embed_norm8(branch_tokens, m->embed, c.vocab, m->layers[0].ln1, c.rms_eps, M,
-                                 Mp, H, ws.x, ws.a8_gu, ws.sa_gu, ws.rowmax_dn, s));
+                                 Mp, H, ws.x, ws.a8_gu, ws.sa_gu, ws.rowmax_dn, zp, s));
     else
       HIP_TRY(launch_embed_norm(branch_tokens, m->embed, c.vocab, m->layers[0].ln1, c.rms_eps, M,
-                                Mp, H, ws.x, ws.abuf, s)); }
+                                Mp, H, ws.x, ws.abuf, zp, s)); }
   AttnArgs at{};
   at.q = ws.qbuf;
   at.staging = kv->staging;
@@ -778,7 +872,7 @@ static int verify_impl(const lopa_model* m, lopa_kv* kv, int32_t prefix_len,
     else
       HIP_TRY(gemm(EPI_LMHEAD, ws.abuf, m->lm, c.vocab, H, plan.lm)); }
   { ProfScope ps_(kv, LOPA_PROF_MERGE, s);
-    HIP_TRY(launch_lm_merge(ws.pm, ws.ps, ws.pi, M, m->tiles_lm, conf, pred, s)); }
+    HIP_TRY(launch_lm_merge(ws.pm, ws.ps, ws.pi, M, plan.lm.tiles, conf, pred, s)); }
   kv->last_nb = n_branches;
   kv->last_L = L;
   kv->last_P = prefix_len;
@@ -1058,45 +1152,18 @@ int verify_with_ws(const lopa_model* m, lopa_kv* kv, int32_t prefix_len,
                      nullptr, ws);
 }
 
-namespace {
-// the regions of a VerifyWs for nb x L rows, in carving order (bytes, each
-// rounded up to 256): x, abuf, fbuf, qbuf, partials, pm, ps, pi, then the FP8
-// operands of FP8 models
-struct WsLayout {
-  size_t sz[13] = {};
-};
-WsLayout ws_layout(const lopa_model* m, int32_t nb, int32_t L) {
-  const lopa_model_cfg& c = m->cfg;
-  const size_t rows = (size_t)padded_rows(nb * L);
-  const int MT = (int)(rows / 256);
-  const StepPlans p = step_plans(m, MT);
-  WsLayout w;
-  w.sz[0] = rows * c.hidden * 4;
-  w.sz[1] = rows * c.hidden * 2;
-  w.sz[2] = rows * round256(c.ffn) * 2;
-  w.sz[3] = (size_t)nb * c.heads * L * c.head_dim * 2;
-  w.sz[4] = std::max({(size_t)16, plan_partial_bytes(EPI_QKV, p.qkv, MT),
-                      plan_partial_bytes(EPI_RESID, p.o, MT), plan_partial_bytes(EPI_RESID, p.down, MT),
-                      attention_scratch_bytes(nb, L, c.heads, c.kv_heads, c.head_dim)});
-  w.sz[5] = w.sz[6] = w.sz[7] = rows * m->tiles_lm * 4;
-  if (m->fp8) {
-    w.sz[8] = rows * round512(c.hidden);
-    w.sz[9] = rows * round512(c.ffn);
-    w.sz[10] = w.sz[11] = w.sz[12] = rows * 4;
-  }
-  for (size_t& v : w.sz) v = (v + 255) / 256 * 256;
-  return w;
-}
-}  // namespace
-
-size_t verify_ws_bytes(const lopa_model* m, int32_t n_branches, int32_t L) {
-  size_t t = 0;
-  for (size_t v : ws_layout(m, n_branches, L).sz) t += v;
-  return t;
+static WsLayout call_layout(const lopa_kv* kv, int32_t nb, int32_t L) {
+  const lopa_model_cfg& c = kv->m->cfg;
+  return ws_layout(kv->m, kv->plans[nb * L], nb * L,
+                   attention_scratch_bytes(nb, L, c.heads, c.kv_heads, c.head_dim));
 }
 
-VerifyWs verify_ws_carve(const lopa_model* m, int32_t n_branches, int32_t L, char* base) {
-  const WsLayout w = ws_layout(m, n_branches, L);
+size_t verify_ws_bytes(const lopa_kv* kv, int32_t n_branches, int32_t L) {
+  return call_layout(kv, n_branches, L).total();
+}
+
+VerifyWs verify_ws_carve(const lopa_kv* kv, int32_t n_branches, int32_t L, char* base) {
+  const WsLayout w = call_layout(kv, n_branches, L);
   char* r[13];
   for (int i = 0; i < 13; ++i) {
     r[i] = base;
@@ -1112,7 +1179,7 @@ VerifyWs verify_ws_carve(const lopa_model* m, int32_t n_branches, int32_t L, cha
   ws.pm = (float*)r[5];
   ws.ps = (float*)r[6];
   ws.pi = (int32_t*)r[7];
-  if (m->fp8) {
+  if (kv->m->fp8) {
     ws.a8_gu = (uint8_t*)r[8];
     ws.a8_dn = (uint8_t*)r[9];
     ws.sa_gu = (float*)r[10];
@@ -1120,24 +1187,4 @@ VerifyWs verify_ws_carve(const lopa_model* m, int32_t n_branches, int32_t L, cha
     ws.rowmax_dn = (uint32_t*)r[12];
   }
   return ws;
-}
-
-int verify_ws_clear_padding(const lopa_model* m, int32_t n_branches, int32_t L, const VerifyWs& ws,
-                            hipStream_t s) {
-  // packed operands are [column block][row block] fragments, so a matrix's
-  // padding columns are one contiguous tail: bf16 blocks of 32 columns x 16
-  // rows (1 KiB), E4M3 blocks of 64 columns x 16 rows (1 KiB)
-  const lopa_model_cfg& c = m->cfg;
-  const size_t rb = (size_t)padded_rows(n_branches * L) / 16;
-  auto tail = [&](void* buf, size_t cols, size_t padded, size_t per_block) -> hipError_t {
-    if (padded == cols) return hipSuccess;
-    const size_t from = cols / per_block * rb * 1024, to = padded / per_block * rb * 1024;
-    return launch_fill_zero((char*)buf + from, to - from, s);
-  };
-  hipError_t e;
-  if ((e = tail(ws.fbuf, c.ffn, round256(c.ffn), 32)) != hipSuccess ||
-      (m->fp8 && ((e = tail(ws.a8_gu, c.hidden, round512(c.hidden), 64)) != hipSuccess ||
-                  (e = tail(ws.a8_dn, c.ffn, round512(c.ffn), 64)) != hipSuccess)))
-    return fail(LOPA_EHIP, "clearing the padding columns: %s", hipGetErrorString(e));
-  return LOPA_OK;
 }

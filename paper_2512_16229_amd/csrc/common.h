@@ -11,11 +11,10 @@
 // Activations ("A" operands, R = padded rows Mp):   fragment (rb, kb) at
 //   ((kb * (Mp/16)) + rb) * 512 elements.
 // Weights (W [N, K] in [out, in] order, "B" operand): blocks of 16 output
-//   features, grouped in tiles of nb consecutive blocks (nb fixed per weight);
-//   each block's 64-column chunk kc is two fragments (kk = 0, 1: columns
-//   32 kk .. +31), fragment (tile t, kc, block j of the tile, kk) at
-//   (((t * (K / 64) + kc) * nb + j) * 2 + kk) * 512. One GEMM iteration of a
-//   tile streams one contiguous nb x 2 KiB chunk.
+//   features; each block's 64-column chunk kc is two fragments (kk = 0, 1:
+//   columns 32 kk .. +31), fragment (kc, block, kk) at
+//   ((kc * blocks + block) * 2 + kk) * 512. One GEMM iteration of a tile of nb
+//   blocks streams one contiguous nb x 2 KiB chunk.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>

@@ -20,16 +20,30 @@
 //           QKV by gemm_fixup_kernel, which also runs the QKV epilogue (QKV
 //           always takes this path).
 //
-// Pipeline. One iteration is a 64-wide k-chunk of one tile. Its NB x 2 KiB of
-// weights go global -> LDS directly (global_load_lds, no registers) into a
-// 6-slot ring, and each wavefront's 8 activation fragments (L2-resident) into
-// one of 4 register sets; both are issued 4 iterations ahead. K is padded to a
-// multiple of 256, so a tile always spans a multiple of 4 iterations and the
-// register set of iteration j is the static j % 4: the loop is unrolled by 4
-// and no register set is ever rotated. Vector memory operations complete in
-// issue order, so "iterations j, j + 1 have landed" is one vmcnt wait on the
-// number of operations issued after them; one workgroup barrier per pair of
-// iterations.
+// What bounds it: the weight stream up to 128 rows (gate/up of the Dream-7B
+// shape, 272 MB: 43.6 us at 32 rows, 6.2 TB/s, against 40-42 us of a copy of the
+// same bytes into LDS and nothing else; the 256-row tile alone took 60 us
+// whatever the rows), and at 256 rows and more the card's power: alone the
+// MFMAs of that projection take 36 us and its memory stream 40, together 60-65,
+// with the clock down from 2.3 GHz (memory alone) to 1.5-1.7 GHz.
+//
+// Row tiles. A workgroup's tile is 64 MB rows (wavefront w: row blocks w MB ..
+// w MB + MB - 1), MB = 1 .. 4 the fewest that cover the call's rows in
+// ceil(rows / 256) tiles: the activation chunk a workgroup pulls per iteration
+// and its MFMAs shrink with it, the weight stream stays.
+//
+// Pipeline. One iteration j is a 64-wide k-chunk of one tile. Its NB x 2 KiB of
+// weights go global -> LDS directly (global_load_lds, no registers) into slot
+// j % RING of a ring, and each wavefront's 2 MB activation fragments
+// (L2-resident) into register set j % 4. Iteration j issues the activation
+// loads of iteration j + 3 and the weight copies of iteration j + RING - 1. K
+// is padded to a multiple of 256, so a tile always spans a multiple of 4
+// iterations and the loop is unrolled by 4: no register set is ever rotated.
+// Vector memory operations complete in issue order, so one vmcnt wait per
+// iteration on the number of operations issued since says that the activations
+// of j and the weights of j and j + 1 have landed; after the workgroup barrier
+// that follows they have for every wavefront, so the weight fragments are read
+// from LDS ahead of their MFMAs across the iteration boundary.
 #include "common.h"
 #include "kernels.h"
 
@@ -38,14 +52,26 @@
 namespace {
 
 constexpr int GEMM_THREADS = 256;
-constexpr int LEAD = 4;         // iterations between issue and use (= activation register sets)
-constexpr int RING = LEAD + 2;  // weight chunks in LDS: a pair in use + LEAD in flight
 
-template <int EPI, int NB>
+// Cache policy of the weight copies, by what the forward measured (us per
+// launch at the Dream-7B shapes, default -> nontemporal): nontemporal where the
+// stream is long or little else is read (gate/up 64.0 -> 60.2, LM head 257 -> 248
+// at 256 rows; every projection at 128 rows and fewer), the default for the
+// short projections of the larger row tiles (down 42.8 -> 45.4, O 18.0 -> 19.8).
+constexpr bool gemm_nt(int epi, int mb) {
+  return epi == EPI_SWIGLU || epi == EPI_LMHEAD || mb <= 2;
+}
+// wavefronts per SIMD the registers are cut for: two workgroups fit a CU's LDS
+// with the narrow tile, and its registers with few row blocks
+constexpr int gemm_waves(int nb, int mb) { return nb == 4 && mb <= 2 ? 2 : 1; }
+
+template <int EPI, int NB, int MB>
 struct GemmSmem {
   static constexpr int CHUNK = NB * 2048;  // bytes of weights per iteration
+  static constexpr int RING = 6;
   static constexpr int BYTES = RING * CHUNK;
-  static_assert(EPI != EPI_LMHEAD || 4 * 64 * 16 * 12 <= RING * CHUNK, "reduction area fits");
+  static_assert(BYTES <= 160 * 1024, "LDS of one CU");
+  static_assert(EPI != EPI_LMHEAD || 4 * 16 * MB * 16 * 12 <= RING * CHUNK, "reduction area fits");
 };
 
 template <int N>
@@ -60,9 +86,7 @@ __device__ __forceinline__ void wait_vmcnt() {
 // the only per-lane address is the constant voff = 16 lane. The compiler does
 // not track the copy: completion is awaited with an explicit vmcnt wait
 // before the workgroup barrier. NT selects the nontemporal (streaming) cache
-// policy: measured per projection, it raises the sustained rate of the long
-// gate/up weight stream (about 7 %) but slows the short ones (QKV, O, down)
-// and the LM head, which keep the default policy.
+// policy (gemm_nt).
 __device__ __forceinline__ const void* uniform_ptr(const void* p) {
   // the "s" constraint alone does not keep a value the compiler thinks may
   // diverge out of VGPRs: make the scalar copy explicit
@@ -83,22 +107,18 @@ __device__ __forceinline__ void lds_dma16(const void* base, uint32_t voff, uint3
                  : "memory");
 }
 
-// Four activation fragments (1 KiB apart) at a wave-uniform base -> registers.
+// One activation fragment at a wave-uniform base + OFF -> registers.
 // Issued as inline assembly so that, like the LDS copies, the compiler does not
 // track them: its own waits would count only the loads it knows of and so
 // stall on younger loads. Nothing reads the registers before the explicit
 // vmcnt wait of the iteration that uses them; pin_landed() then hands them to
 // the compiler.
-__device__ __forceinline__ void load_frag4(u32x4& d0, u32x4& d1, u32x4& d2, u32x4& d3,
-                                           const void* base, uint32_t voff) {
-  asm volatile(
-      "global_load_dwordx4 %0, %4, %5\n\t"
-      "global_load_dwordx4 %1, %4, %5 offset:1024\n\t"
-      "global_load_dwordx4 %2, %4, %5 offset:2048\n\t"
-      "global_load_dwordx4 %3, %4, %5 offset:3072"
-      : "=&v"(d0), "=&v"(d1), "=&v"(d2), "=&v"(d3)
-      : "v"(voff), "s"(uniform_ptr(base))
-      : "memory");
+template <int OFF>
+__device__ __forceinline__ void load_frag(u32x4& d, const void* base, uint32_t voff) {
+  asm volatile("global_load_dwordx4 %0, %1, %2 offset:%3"
+               : "=&v"(d)
+               : "v"(voff), "s"(uniform_ptr(base)), "n"(OFF)
+               : "memory");
 }
 __device__ __forceinline__ void pin_landed(u32x4& v) { asm volatile("" : "+v"(v)); }
 // After the loop the last iterations' loads (repeats of the last chunk) are
@@ -107,7 +127,7 @@ __device__ __forceinline__ void pin_landed(u32x4& v) { asm volatile("" : "+v"(v)
 #define GEMM_DRAIN()                                                                     \
   {                                                                                      \
     wait_vmcnt<0>();                                                                     \
-    _Pragma("unroll") for (int i_ = 0; i_ < 8; ++i_) {                                   \
+    _Pragma("unroll") for (int i_ = 0; i_ < 2 * MB; ++i_) {                              \
       pin_landed(a0[i_]);                                                                \
       pin_landed(a1[i_]);                                                                \
       pin_landed(a2[i_]);                                                                \
@@ -147,15 +167,15 @@ __device__ __forceinline__ void mfma_settle() {
 
 // FP8: the accumulated products times the row's and the column's scales
 // (acc[mb][nb][j]: row row0 + 16 mb + 4 g + j, packed column 16 (tile NB + nb) + c16)
-template <int NB>
-__device__ __forceinline__ void f8_scale(const GemmArgs& a, f32x4 (&acc)[4][NB], int tile,
+template <int NB, int MB>
+__device__ __forceinline__ void f8_scale(const GemmArgs& a, f32x4 (&acc)[MB][NB], int tile,
                                          int row0, int lane) {
   const int g = lane >> 4, c16 = lane & 15;
   float swc[NB];
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) swc[nb] = a.sw[(tile * NB + nb) * 16 + c16];
 #pragma unroll
-  for (int mb = 0; mb < 4; ++mb)
+  for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const float sr = a.sa[row0 + mb * 16 + g * 4 + j];
@@ -164,12 +184,12 @@ __device__ __forceinline__ void f8_scale(const GemmArgs& a, f32x4 (&acc)[4][NB],
     }
 }
 
-template <int NB>
-__device__ __forceinline__ void resid_epilogue(const GemmArgs& a, f32x4 (&acc)[4][NB], int tile,
+template <int NB, int MB>
+__device__ __forceinline__ void resid_epilogue(const GemmArgs& a, f32x4 (&acc)[MB][NB], int tile,
                                                int row0, int lane) {
   const int g = lane >> 4, c16 = lane & 15;
 #pragma unroll
-  for (int mb = 0; mb < 4; ++mb)
+  for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int r = row0 + mb * 16 + g * 4 + j;
@@ -194,13 +214,13 @@ __device__ __forceinline__ void resid_epilogue(const GemmArgs& a, f32x4 (&acc)[4
 // halves with one permlane swap per dword: afterwards the even lane holds the
 // slot of row block mb, the odd lane the slot of row block mb + 1, and each
 // writes 16 bytes.
-template <int NB, bool F8>
-__device__ __forceinline__ void swiglu_epilogue(const GemmArgs& a, f32x4 (&acc)[4][NB], int tile,
+template <int NB, int MB, bool F8>
+__device__ __forceinline__ void swiglu_epilogue(const GemmArgs& a, f32x4 (&acc)[MB][NB], int tile,
                                                 int row0, int lane) {
   constexpr int PAIRS = NB / 2;
   const int g = lane >> 4, c16 = lane & 15;
   const int Nout = a.N >> 1;
-  float mxr[4] = {0.f, 0.f, 0.f, 0.f};  // FP8: largest |output| of each row block's row
+  float mxr[MB] = {};  // FP8: largest |output| of each row block's row
   auto swiglu4 = [&](int mb, int p, uint32_t (&hv)[2]) {
     // FP8: scales of the row (this lane's) and of the gate / up columns
     const float sr = F8 ? a.sa[row0 + mb * 16 + c16] : 1.f;
@@ -222,11 +242,12 @@ __device__ __forceinline__ void swiglu_epilogue(const GemmArgs& a, f32x4 (&acc)[
       }
       hv[jj] = (uint32_t)f2bf_bits(h2[0]) | ((uint32_t)f2bf_bits(h2[1]) << 16);
       if constexpr (F8)
-        mxr[mb] = fmaxf(mxr[mb], fmaxf(fabsf(bf2f_bits(hv[jj] & 0xffffu)), fabsf(bf2f_bits(hv[jj] >> 16))));
+        if ((tile * PAIRS + p) * 16 < Nout)  // columns past the last block: not stored, not counted
+          mxr[mb] = fmaxf(mxr[mb], fmaxf(fabsf(bf2f_bits(hv[jj] & 0xffffu)), fabsf(bf2f_bits(hv[jj] >> 16))));
     }
   };
 #pragma unroll
-  for (int mp = 0; mp < 2; ++mp) {
+  for (int mp = 0; mp < MB / 2; ++mp) {
     const int r = row0 + (2 * mp + (g & 1)) * 16 + c16;
 #pragma unroll
     for (int p = 0; p < PAIRS; ++p) {
@@ -240,12 +261,25 @@ __device__ __forceinline__ void swiglu_epilogue(const GemmArgs& a, f32x4 (&acc)[
         *(uint4*)(a.a_out + packA_off(r, col, a.Mp)) = make_uint4(w0[0], w1[0], w0[1], w1[1]);
     }
   }
+  if constexpr (MB & 1) {
+    // the last row block of an odd count has no partner: each lane writes its
+    // four columns (8 bytes, half a slot)
+    const int r = row0 + (MB - 1) * 16 + c16;
+#pragma unroll
+    for (int p = 0; p < PAIRS; ++p) {
+      uint32_t h0[2];
+      swiglu4(MB - 1, p, h0);
+      const int col = (tile * PAIRS + p) * 16 + 4 * g;
+      if (r < a.M && col < Nout)
+        *(uint2*)(a.a_out + packA_off(r, col, a.Mp)) = make_uint2(h0[0], h0[1]);
+    }
+  }
   if constexpr (F8) {
     // the row maxima of this tile's outputs (the stored bf16 values) into the
     // per-row maximum over all tiles: the lanes c16 + 16 g hold the same row;
     // an unsigned maximum of the bits orders non-negative floats exactly
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb) {
+    for (int mb = 0; mb < MB; ++mb) {
       float m = fmaxf(mxr[mb], __shfl_xor(mxr[mb], 16));
       m = fmaxf(m, __shfl_xor(m, 32));
       const int r = row0 + mb * 16 + c16;
@@ -257,18 +291,19 @@ __device__ __forceinline__ void swiglu_epilogue(const GemmArgs& a, f32x4 (&acc)[
 // per-row (max, argmax, sum exp(l - max)) over this tile's valid columns
 // (column < vocab, column != mask token) -> pm / ps / pi [row][tile]. Each lane
 // first reduces its NB columns of each of its 16 rows; the 16 lane partials of
-// a row then meet in LDS (red: this wavefront's 64 x 16 x 3 words) and one lane
+// a row then meet in LDS (red: this wavefront's 16 MB x 16 x 3 words) and one lane
 // per row merges them in column order (ties: lowest column).
-template <int NB>
-__device__ __forceinline__ void lm_epilogue(const GemmArgs& a, f32x4 (&acc)[4][NB], int tile,
+template <int NB, int MB>
+__device__ __forceinline__ void lm_epilogue(const GemmArgs& a, f32x4 (&acc)[MB][NB], int tile,
                                             int row0, int lane, float* red) {
   constexpr float LOG2E = 1.4426950408889634f;
   const int g = lane >> 4, c16 = lane & 15;
   float* rm = red;
-  float* rs = red + 64 * 16;
-  int* ri = (int*)(red + 2 * 64 * 16);
+  constexpr int ROWS = 16 * MB;
+  float* rs = red + ROWS * 16;
+  int* ri = (int*)(red + 2 * ROWS * 16);
 #pragma unroll
-  for (int mb = 0; mb < 4; ++mb)
+  for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       float m = -INFINITY;
@@ -296,8 +331,9 @@ __device__ __forceinline__ void lm_epilogue(const GemmArgs& a, f32x4 (&acc)[4][N
   int I = 0x7fffffff;
 #pragma unroll
   for (int c = 0; c < 16; ++c) {
-    const float mc = rm[lane * 16 + c], sc = rs[lane * 16 + c];
-    const int ic = ri[lane * 16 + c];
+    const int o = (lane < ROWS ? lane : 0) * 16 + c;
+    const float mc = rm[o], sc = rs[o];
+    const int ic = ri[o];
     if (mc > M) {
       S = S * __builtin_amdgcn_exp2f((M - mc) * LOG2E) + sc;
       M = mc;
@@ -310,7 +346,7 @@ __device__ __forceinline__ void lm_epilogue(const GemmArgs& a, f32x4 (&acc)[4][N
     }
   }
   const int r = row0 + lane;
-  if (r < a.M) {
+  if (lane < ROWS && r < a.M) {
     const int64_t o = (int64_t)r * a.tiles + tile;
     a.pm[o] = M;
     a.ps[o] = M == -INFINITY ? 0.f : S;
@@ -319,150 +355,116 @@ __device__ __forceinline__ void lm_epilogue(const GemmArgs& a, f32x4 (&acc)[4][N
 }
 
 // ------------------------------------------------------------------ main loop
-// Loads of one iteration: 8 activation fragments into register set `set` (two
-// groups of 4, k-halves 0 and 1) and the NB x 2 KiB weight chunk into ring
-// slot `slot` (NB / 2 copies of 1 KiB per wavefront). Weight layout
-// [tile][KC][NB][2][64 lanes][8]: the chunk of iteration (tile, kc) is one
-// contiguous run, and so is a tile's whole k-range. The addresses advance by
-// one k-chunk per issued iteration (a_next, w_next), from kc0 to the end of the
-// range and then from its start (rotation, GemmArgs::rot); after the last of
-// the range's iterations the last chunk is issued again (an L2 hit), which keeps
-// every wait count constant and the loop branch-free.
-#define GEMM_ISSUE_A(set, half)                                                          \
-  load_frag4(set[4 * (half) + 0], set[4 * (half) + 1], set[4 * (half) + 2],              \
-             set[4 * (half) + 3], a_next + (half) * a_half, voff)
+// Loads of one iteration: 2 MB activation fragments into register set `set`
+// (two groups of MB, k-halves 0 and 1) and the NB x 2 KiB weight chunk into
+// ring slot `slot` (NB / 2 copies of 1 KiB per wavefront). Weight layout
+// [KC][blocks][2][64 lanes][8]: the chunk of (tile, kc) is one contiguous run,
+// and the workgroups, which advance in step, read neighbouring runs at a time.
+// The activation and the weight addresses advance by one k-chunk per issued
+// iteration, from kc0 to the end of the range and then from its start
+// (rotation, GemmArgs::rot); after the last of the range's iterations the last
+// chunk is issued again (an L2 hit), which keeps every wait count constant and
+// the loop branch-free.
+#define GEMM_ISSUE_A(set, i) /* fragment i < 2 MB: row block i % MB, k-half i / MB */    \
+  switch ((i) % MB) {                                                                    \
+    case 0: load_frag<0>(set[i], a_next + ((i) / MB) * a_half, voff); break;             \
+    case 1: load_frag<1024>(set[i], a_next + ((i) / MB) * a_half, voff); break;          \
+    case 2: load_frag<2048>(set[i], a_next + ((i) / MB) * a_half, voff); break;          \
+    case 3: load_frag<3072>(set[i], a_next + ((i) / MB) * a_half, voff); break;          \
+  }
 #define GEMM_ISSUE_W(r, slot)                                                            \
-  lds_dma16<EPI == EPI_SWIGLU>(w_next + (r) * 4096, voff,                              \
-            lds_wave + (uint32_t)(slot) * (uint32_t)SM::CHUNK + (uint32_t)(r) * 4096u)
-#define GEMM_ADVANCE_LOAD()                                                              \
+  lds_dma16<NT>(w_next + (r) * 4096, voff,                                               \
+                lds_wave + (uint32_t)(slot) * (uint32_t)SM::CHUNK + (uint32_t)(r) * 4096u)
+#define GEMM_ADVANCE(next, step, back, li, lk)                                           \
   {                                                                                      \
-    if (li + 1 < n_it) {                                                                 \
-      ++li;                                                                              \
-      if (lk + 1 < kc_end) {                                                             \
-        ++lk;                                                                            \
-        a_next += a_kstep;                                                               \
-        w_next += SM::CHUNK;                                                             \
-      } else {                                                                           \
-        lk = kc_beg;                                                                     \
-        a_next -= (int64_t)(n_it - 1) * a_kstep;                                         \
-        w_next -= (int64_t)(n_it - 1) * SM::CHUNK;                                       \
-      }                                                                                  \
-    }                                                                                    \
+    const bool more_ = li + 1 < n_it, wrap_ = lk + 1 == kc_end;                          \
+    const int64_t d_ = wrap_ ? -back : step;                                             \
+    next += more_ ? d_ : 0;                                                              \
+    lk = more_ ? (wrap_ ? kc_beg : lk + 1) : lk;                                         \
+    ++li;                                                                                \
   }
-#define GEMM_ISSUE(set, slot)                                                            \
+#define GEMM_ISSUE_A_ALL(set)                                                            \
   {                                                                                      \
-    GEMM_ISSUE_A(set, 0);                                                                \
-    GEMM_ISSUE_A(set, 1);                                                                \
+    _Pragma("unroll") for (int i_ = 0; i_ < 2 * MB; ++i_) GEMM_ISSUE_A(set, i_);         \
+    GEMM_ADVANCE(a_next, a_kstep, a_back, lia, lka);                                             \
+  }
+#define GEMM_ISSUE_W_ALL(slot)                                                           \
+  {                                                                                      \
     _Pragma("unroll") for (int r_ = 0; r_ < NB / 2; ++r_) GEMM_ISSUE_W(r_, slot);        \
-    GEMM_ADVANCE_LOAD();                                                                 \
+    GEMM_ADVANCE(w_next, w_kstep, w_back, liw, lkw);                                             \
   }
 
-// Two iterations j, j + 1 per workgroup barrier. Their 4 NB weight fragments
-// are read from LDS BPF fragments ahead of the MFMAs that use them (across
-// the iteration boundary); the loads of iterations j + 4 and j + 5 are spread
-// over the MFMA stream (an activation half once the MFMAs reading it have
-// issued, the weight copies from the second fragment of each iteration on).
-// Scheduling barriers keep this order. Every iteration issues exactly OPS
-// operations, so "j and j + 1 have landed" is vmcnt(2 OPS); the slots written
-// here held iterations j - 2 and j - 1, which every wavefront finished before
-// this barrier.
-constexpr int BPF = 4;
-#define GEMM_PAIR(s0, s1)                                                                \
+// Iteration j on register set `cur` (j % 4), issuing the activations of j + 3
+// into `nxt` ((j + 3) % 4, last read by iteration j - 1) and the weights of
+// j + RING - 1 into the slot that iteration j - 1 read (every wavefront is past
+// it after this barrier). Its 2 NB weight fragments f are read from LDS BPF
+// ahead of their MFMAs into bf[f % BPF], the last BPF reads being the next
+// iteration's first fragments. The loads are spread evenly over the MFMA stream (a wavefront
+// that waits for a full memory queue issues no MFMA);
+// scheduling barriers keep the order. FP8: a fragment covers 64 values of K (16
+// per lane) and they are read in (block, half) order, so that both halves of a
+// block are in registers together; each block takes one 16x16x128 MFMA per row
+// block. In bf16 the order is (half, block).
+#define GEMM_LDS_FRAG(slot, f)                                                           \
+  ((const u32x4*)(smem + (slot) * SM::CHUNK))[(F8 ? (f) : ((f) % NB) * 2 + (f) / NB) * 64 + lane]
+#define GEMM_ITER(cur, nxt)                                                              \
   {                                                                                      \
-    wait_vmcnt<2 * OPS>();                                                               \
+    wait_vmcnt<WAIT>();                                                                  \
     lds_barrier();                                                                       \
-    _Pragma("unroll") for (int i_ = 0; i_ < 8; ++i_) {                                   \
-      pin_landed(s0[i_]);                                                                \
-      pin_landed(s1[i_]);                                                                \
-    }                                                                                    \
-    const u32x4* wl0_ = (const u32x4*)(smem + cs * SM::CHUNK);                           \
-    const int c1_ = cs + 1 == RING ? 0 : cs + 1;                                         \
-    const u32x4* wl1_ = (const u32x4*)(smem + c1_ * SM::CHUNK);                          \
-    const int is0_ = cs >= 2 ? cs - 2 : cs + RING - 2; /* slot of iteration j - 2 */    \
-    const int is1_ = is0_ + 1 == RING ? 0 : is0_ + 1;                                    \
-    u32x4 bf_[4 * NB];                                                                   \
-    _Pragma("unroll") for (int f_ = 0; f_ < BPF; ++f_)                                   \
-      bf_[f_] = wl0_[((f_ % NB) * 2 + f_ / NB) * 64 + lane];                             \
+    _Pragma("unroll") for (int i_ = 0; i_ < 2 * MB; ++i_) pin_landed(cur[i_]);           \
+    const int ns_ = cs + 1 == SM::RING ? 0 : cs + 1;                                     \
+    const int is_ = cs == 0 ? SM::RING - 1 : cs - 1;                                     \
     __builtin_amdgcn_sched_barrier(0);                                                   \
-    _Pragma("unroll") for (int f_ = 0; f_ < 4 * NB; ++f_) {                              \
-      const int e_ = f_ / (2 * NB), g_ = f_ % (2 * NB); /* iteration, fragment */        \
-      if (f_ + BPF < 4 * NB) {                                                           \
-        const int fn_ = f_ + BPF, gn_ = fn_ % (2 * NB);                                  \
-        bf_[fn_] = (fn_ < 2 * NB ? wl0_ : wl1_)[((gn_ % NB) * 2 + gn_ / NB) * 64 + lane];  \
-      }                                                                                  \
-      _Pragma("unroll") for (int mb_ = 0; mb_ < 4; ++mb_)                                \
-        if constexpr (EPI == EPI_SWIGLU) /* transposed tile: lanes hold output rows */  \
-          mfma_acc(acc[mb_][g_ % NB], bf_[f_], (e_ ? s1 : s0)[(g_ / NB) * 4 + mb_]);     \
-        else                                                                             \
-          mfma_acc(acc[mb_][g_ % NB], (e_ ? s1 : s0)[(g_ / NB) * 4 + mb_], bf_[f_]);     \
-      if (g_ >= 1 && g_ <= NB / 2) GEMM_ISSUE_W(g_ - 1, e_ ? is1_ : is0_);               \
-      if (g_ == NB - 1) GEMM_ISSUE_A((e_ ? s1 : s0), 0);                                 \
-      if (g_ == 2 * NB - 1) {                                                            \
-        GEMM_ISSUE_A((e_ ? s1 : s0), 1);                                                 \
-        GEMM_ADVANCE_LOAD();                                                             \
-      }                                                                                  \
-      __builtin_amdgcn_sched_barrier(0);                                                 \
-    }                                                                                    \
-    cs = cs + 2 >= RING ? cs + 2 - RING : cs + 2;                                        \
-  }
-
-// FP8 form of GEMM_PAIR: a weight unit (block, k-half) covers 64 values of K
-// (16 per lane), and the units are read in (block, half) order, so both halves
-// of a block are in registers together; each block then takes one 16x16x128 MFMA per
-// row block with both activation halves as its first operand. The activation
-// set of an iteration is read until its last block, so both halves are
-// reissued at the end of the iteration (the weight copies as in GEMM_PAIR).
-#define GEMM_PAIR_F8(s0, s1)                                                             \
-  {                                                                                      \
-    wait_vmcnt<2 * OPS>();                                                               \
-    lds_barrier();                                                                       \
-    _Pragma("unroll") for (int i_ = 0; i_ < 8; ++i_) {                                   \
-      pin_landed(s0[i_]);                                                                \
-      pin_landed(s1[i_]);                                                                \
-    }                                                                                    \
-    const u32x4* wl0_ = (const u32x4*)(smem + cs * SM::CHUNK);                           \
-    const int c1_ = cs + 1 == RING ? 0 : cs + 1;                                         \
-    const u32x4* wl1_ = (const u32x4*)(smem + c1_ * SM::CHUNK);                          \
-    const int is0_ = cs >= 2 ? cs - 2 : cs + RING - 2;                                   \
-    const int is1_ = is0_ + 1 == RING ? 0 : is0_ + 1;                                    \
-    u32x4 bf_[4 * NB];                                                                   \
-    _Pragma("unroll") for (int f_ = 0; f_ < BPF; ++f_) bf_[f_] = wl0_[f_ * 64 + lane];    \
-    __builtin_amdgcn_sched_barrier(0);                                                   \
-    _Pragma("unroll") for (int f_ = 0; f_ < 4 * NB; ++f_) {                              \
-      const int e_ = f_ / (2 * NB), g_ = f_ % (2 * NB); /* iteration, unit */           \
-      if (f_ + BPF < 4 * NB) {                                                           \
-        const int fn_ = f_ + BPF, gn_ = fn_ % (2 * NB);                                  \
-        bf_[fn_] = (fn_ < 2 * NB ? wl0_ : wl1_)[gn_ * 64 + lane];                        \
-      }                                                                                  \
-      if (g_ & 1) {                                                                      \
-        const u32x8 b8_ = cat8(bf_[f_ - 1], bf_[f_]);                                    \
-        _Pragma("unroll") for (int mb_ = 0; mb_ < 4; ++mb_) {                            \
-          const u32x8 a8_ = cat8((e_ ? s1 : s0)[mb_], (e_ ? s1 : s0)[4 + mb_]);          \
-          if constexpr (EPI == EPI_SWIGLU)                                               \
-            mfma_acc_f8(acc[mb_][g_ >> 1], b8_, a8_);                                    \
-          else                                                                           \
-            mfma_acc_f8(acc[mb_][g_ >> 1], a8_, b8_);                                    \
+    _Pragma("unroll") for (int f_ = 0; f_ < 2 * NB; ++f_) {                              \
+      if constexpr (F8) {                                                                \
+        if (f_ & 1) {                                                                    \
+          const u32x8 b8_ = cat8(bf[(f_ - 1) % BPF], bf[f_ % BPF]);                      \
+          _Pragma("unroll") for (int mb_ = 0; mb_ < MB; ++mb_) {                         \
+            const u32x8 a8_ = cat8(cur[mb_], cur[MB + mb_]);                             \
+            if constexpr (EPI == EPI_SWIGLU)                                             \
+              mfma_acc_f8(acc[mb_][f_ >> 1], b8_, a8_);                                  \
+            else                                                                         \
+              mfma_acc_f8(acc[mb_][f_ >> 1], a8_, b8_);                                  \
+          }                                                                              \
+          _Pragma("unroll") for (int u_ = f_ - 1; u_ <= f_; ++u_)                        \
+            bf[u_ % BPF] = GEMM_LDS_FRAG(u_ + BPF < 2 * NB ? cs : ns_, (u_ + BPF) % (2 * NB)); \
         }                                                                                \
+      } else {                                                                           \
+        _Pragma("unroll") for (int mb_ = 0; mb_ < MB; ++mb_)                             \
+          if constexpr (EPI == EPI_SWIGLU) /* transposed tile: lanes hold output rows */ \
+            mfma_acc(acc[mb_][f_ % NB], bf[f_ % BPF], cur[(f_ / NB) * MB + mb_]);        \
+          else                                                                           \
+            mfma_acc(acc[mb_][f_ % NB], cur[(f_ / NB) * MB + mb_], bf[f_ % BPF]);        \
+        bf[f_ % BPF] = GEMM_LDS_FRAG(f_ + BPF < 2 * NB ? cs : ns_, (f_ + BPF) % (2 * NB)); \
       }                                                                                  \
-      if (g_ >= 1 && g_ <= NB / 2) GEMM_ISSUE_W(g_ - 1, e_ ? is1_ : is0_);               \
-      if (g_ == 2 * NB - 1) {                                                            \
-        GEMM_ISSUE_A((e_ ? s1 : s0), 0);                                                 \
-        GEMM_ISSUE_A((e_ ? s1 : s0), 1);                                                 \
-        GEMM_ADVANCE_LOAD();                                                             \
-      }                                                                                  \
+      _Pragma("unroll") for (int o_ = 0; o_ < OPS; ++o_)                                 \
+        if (o_ * 2 * NB / OPS == f_) {                                                   \
+          if (o_ < 2 * MB) {                                                             \
+            GEMM_ISSUE_A(nxt, o_);                                                       \
+            if (o_ == 2 * MB - 1) GEMM_ADVANCE(a_next, a_kstep, a_back, lia, lka);       \
+          } else {                                                                       \
+            GEMM_ISSUE_W(o_ - 2 * MB, is_);                                              \
+            if (o_ == OPS - 1) GEMM_ADVANCE(w_next, w_kstep, w_back, liw, lkw);          \
+          }                                                                              \
+        }                                                                                \
       __builtin_amdgcn_sched_barrier(0);                                                 \
     }                                                                                    \
-    cs = cs + 2 >= RING ? cs + 2 - RING : cs + 2;                                        \
+    cs = ns_;                                                                            \
   }
 
-template <int EPI, int NB, bool F8>
-__global__ __launch_bounds__(GEMM_THREADS, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) void gemm_kernel(GemmArgs a) {
-  using SM = GemmSmem<EPI, NB>;
+template <int EPI, int NB, int MB, bool F8>
+__global__ __launch_bounds__(GEMM_THREADS, 1) __attribute__((amdgpu_waves_per_eu(gemm_waves(NB, MB), gemm_waves(NB, MB)))) void gemm_kernel(GemmArgs a) {
+  using SM = GemmSmem<EPI, NB, MB>;
   // FP8: the epilogues of RESID and LMHEAD take scaled sums (f8_scale), SWIGLU
   // scales inside its epilogue, QKV in the fix-up (its partial sums are raw)
-  constexpr int OPS = 8 + NB / 2;  // vector memory operations per wavefront per iteration
-  static_assert(NB % 2 == 0 && 3 * OPS <= 63, "tile width");
-  static_assert(RING == 6 && LEAD == 4, "pair schedule");
+  constexpr int OPS = 2 * MB + NB / 2;  // vector memory operations per wavefront per iteration
+  // operations in flight at the top of iteration j: those of the last two
+  // iterations (activations of j + 1 and j + 2, weights of j + 3 and j + 4)
+  constexpr int WAIT = 2 * OPS;
+  constexpr int BPF = MB >= 3 ? 4 : NB == 10 ? 10 : 8;  // fragments read ahead (LDS latency)
+  constexpr bool NT = gemm_nt(EPI, MB);
+  static_assert(NB % 2 == 0 && NB <= GEMM_MAX_NB && SM::RING == 6, "tile");
+  static_assert(WAIT <= 63 && 2 * NB % BPF == 0, "pipeline");
   __shared__ __attribute__((aligned(1024))) char smem[SM::BYTES];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -489,8 +491,8 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) __attribute__((amdgpu_waves_per_eu
   if (t_lo >= a.tiles || kc_beg >= kc_end) return;
   const int nq = (kc_end - kc_beg) >> 2;  // quads of iterations per tile
   const int RB = a.Mp >> 4;
-  const int rb0 = mt * 16 + wv * 4;     // first 16-row block of this wavefront
-  const int row0 = mt * 256 + wv * 64;  // first row of this wavefront
+  const int rb0 = (mt * 4 + wv) * MB;  // first 16-row block of this wavefront
+  const int row0 = rb0 * 16;           // first row of this wavefront
   const uint32_t voff = (uint32_t)lane * 16u;
   // activation fragment (kb, rb) at A + ((kb RB) + rb) KiB: k-chunk kc, half h
   // of this wavefront's first row block -> a_next + h a_half
@@ -498,52 +500,64 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) __attribute__((amdgpu_waves_per_eu
   const int n_it = kc_end - kc_beg;  // iterations of this workgroup
   const int kc0 = kc_beg + (a.rot ? 4 * (t_lo % nq) : 0);  // first k-chunk
   const char* a_next = (const char*)a.A + ((int64_t)2 * kc0 * RB + rb0) * 1024;
-  // weight chunk (tile, kc) at W + (tile KC + kc) CHUNK; its 1 KiB unit u (block
-  // u / 2, k-half u % 2) at + u KiB; wavefront wv copies units 4 r + wv
-  const char* w_next = (const char*)a.W + ((int64_t)t_lo * KC + kc0) * SM::CHUNK + wv * 1024;
+  // weight chunk (tile, kc) at W + (kc blocks + tile NB) 2 KiB; its 1 KiB unit u
+  // (block u / 2, k-half u % 2) at + u KiB; wavefront wv copies units 4 r + wv
+  const int64_t w_kstep = (int64_t)a.wblocks * 2048;
+  const char* w_next = (const char*)a.W + kc0 * w_kstep + (int64_t)t_lo * SM::CHUNK + wv * 1024;
   const uint32_t lds_wave = sW_base + (uint32_t)wv * 1024u;
-  int lk = kc0;  // k-chunk of the next iteration to issue
-  int li = 0;    // iterations issued before it
+  const int64_t a_back = (n_it - 1) * a_kstep, w_back = (n_it - 1) * w_kstep;  // range end -> start
+  int lka = kc0, lkw = kc0;  // k-chunk of the next iteration to issue (activations, weights)
+  int lia = 0, liw = 0;      // iterations issued before it
 
-  f32x4 acc[4][NB];
-  u32x4 a0[8], a1[8], a2[8], a3[8];
-  GEMM_ISSUE(a0, 0);
-  GEMM_ISSUE(a1, 1);
-  GEMM_ISSUE(a2, 2);
-  GEMM_ISSUE(a3, 3);
+  f32x4 acc[MB][NB];
+  u32x4 a0[2 * MB], a1[2 * MB], a2[2 * MB], a3[2 * MB];
+  u32x4 bf[BPF];
+  GEMM_ISSUE_W_ALL(0);
+  GEMM_ISSUE_W_ALL(1);
+  GEMM_ISSUE_A_ALL(a0);
+  GEMM_ISSUE_W_ALL(2);
+  GEMM_ISSUE_A_ALL(a1);
+  GEMM_ISSUE_W_ALL(3);
+  GEMM_ISSUE_A_ALL(a2);
+  GEMM_ISSUE_W_ALL(4);
   int cs = 0;  // ring slot of the current iteration
 
   {
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb)
+    for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
     mfma_settle();
-    for (int qq = 0; qq < nq; ++qq) {
-      if constexpr (F8) {
-        GEMM_PAIR_F8(a0, a1);
-        GEMM_PAIR_F8(a2, a3);
-      } else {
-        GEMM_PAIR(a0, a1);
-        GEMM_PAIR(a2, a3);
-      }
-    }
+    // the first iteration's first fragments
+    wait_vmcnt<WAIT>();
+    lds_barrier();
+#pragma unroll
+    for (int f = 0; f < BPF; ++f) bf[f] = GEMM_LDS_FRAG(0, f);
+    int qq = nq;
+    do {
+      GEMM_ITER(a0, a3);
+      GEMM_ITER(a1, a0);
+      GEMM_ITER(a2, a1);
+      GEMM_ITER(a3, a2);
+    } while (--qq > 0);
     GEMM_DRAIN();
     mfma_settle();
-    if constexpr (F8 && (EPI == EPI_RESID || EPI == EPI_LMHEAD)) f8_scale<NB>(a, acc, t_lo, row0, lane);
+    if constexpr (F8 && (EPI == EPI_RESID || EPI == EPI_LMHEAD))
+      f8_scale<NB, MB>(a, acc, t_lo, row0, lane);
     if (EPI != EPI_QKV && a.splits == 1) {
       if constexpr (EPI == EPI_LMHEAD) {
         lds_barrier();  // the ring becomes the reduction area (every copy has landed)
-        lm_epilogue<NB>(a, acc, t_lo, row0, lane, (float*)smem + wv * 64 * 16 * 3);
+        lm_epilogue<NB, MB>(a, acc, t_lo, row0, lane, (float*)smem + wv * 16 * MB * 16 * 3);
       }
-      if constexpr (EPI == EPI_RESID) resid_epilogue<NB>(a, acc, t_lo, row0, lane);
-      if constexpr (EPI == EPI_SWIGLU) swiglu_epilogue<NB, F8>(a, acc, t_lo, row0, lane);
+      if constexpr (EPI == EPI_RESID) resid_epilogue<NB, MB>(a, acc, t_lo, row0, lane);
+      if constexpr (EPI == EPI_SWIGLU) swiglu_epilogue<NB, MB, F8>(a, acc, t_lo, row0, lane);
     } else if constexpr (EPI == EPI_RESID) {
       // row-major partial sums [split][Mp][N], added by the following RMSNorm
       const int g = lane >> 4, c16 = lane & 15;
       float* part = a.partials + (int64_t)split * a.Mp * a.N;
 #pragma unroll
-      for (int mb = 0; mb < 4; ++mb)
+      for (int mb = 0; mb < MB; ++mb)
+        if (row0 + mb * 16 < a.M)  // row blocks of padding alone are never read
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           float* pr = part + (int64_t)(row0 + mb * 16 + g * 4 + j) * a.N;
@@ -555,9 +569,9 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) __attribute__((amdgpu_waves_per_eu
         }
     } else {
       const int64_t slot = ((int64_t)mt * a.tiles + t_lo) * a.splits + split;
-      f32x4* part = (f32x4*)a.partials + (slot * 4 + wv) * 4 * NB * 64;
+      f32x4* part = (f32x4*)a.partials + (slot * 4 + wv) * MB * NB * 64;
 #pragma unroll
-      for (int mb = 0; mb < 4; ++mb)
+      for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) part[(mb * NB + nb) * 64 + lane] = acc[mb][nb];
     }
@@ -566,43 +580,37 @@ __global__ __launch_bounds__(GEMM_THREADS, 1) __attribute__((amdgpu_waves_per_eu
 }
 
 // QKV: sum the S partials of one f32x4 of the output (4 rows, 1 column) in
-// split order and run the epilogue. One thread per (row tile, column tile, wave,
-// 16-row block, 16-column block, lane): the same indexing as gemm_kernel's
-// partial store, so each warp-wide load is 1 KiB contiguous. The split count SC
-// (1..8, QKV_MAX_SPLITS) is a constant, so that every load of a thread (the
-// split sums of its column and of its rotation partner, the rotary rows, bias
-// and scales) is in flight before the first add.
-template <int EPI, int NB, int SC>
+// split order and run the epilogue. A wavefront per (row block, 16-column block),
+// the same indexing as gemm_kernel's partial store, so each wavefront's load is
+// 1 KiB contiguous. The split count SC (1..8, QKV_MAX_SPLITS) is a constant, so
+// that every load of a thread (the split sums of its column and of its rotation
+// partner, the rotary rows, bias and scales) is in flight before the first add.
+template <int SC>
 __global__ __launch_bounds__(256) void gemm_fixup_kernel(GemmArgs a) {
-  const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int lane = (int)(gid & 63);
-  int64_t rest = gid >> 6;
-  const int nb = (int)(rest % NB);
-  rest /= NB;
-  const int mb = (int)(rest & 3);
-  rest >>= 2;
-  const int wv = (int)(rest & 3);
-  rest >>= 2;
-  const int tile = (int)(rest % a.tiles);
-  const int mt = (int)(rest / a.tiles);
-  if (mt >= a.mtiles) return;
+  const int lane = threadIdx.x & 63;
+  const int blk = blockIdx.y * 4 + (threadIdx.x >> 6);  // 16-column block
+  const int NB = a.nb, MB = a.mb, lnb = 31 - __builtin_clz(NB);  // NB a power of two
+  // row block blockIdx.x of row tile mt: wavefront wv, its block mb
+  const int mt = blockIdx.z, wm = blockIdx.x;
+  const int wv = (wm >= MB) + (wm >= 2 * MB) + (wm >= 3 * MB), mb = wm - wv * MB;
   const int g = lane >> 4, c16 = lane & 15;
-  const int r0 = mt * 256 + wv * 64 + mb * 16 + g * 4;
-  const int n = (tile * NB + nb) * 16 + c16;
+  const int r0 = (mt * 4 * MB + wm) * 16 + g * 4;
+  const int n = blk * 16 + c16;
   if (n >= a.N || r0 >= a.M) return;
   const int D = a.d, HD = D >> 1;
   const int qcols = a.Hq * D, kcols = a.Hkv * D;
   const int sect = n < qcols ? 0 : (n < qcols + kcols ? 1 : 2);
   const int base = sect == 0 ? 0 : (sect == 1 ? qcols : qcols + kcols);
-  const int head = (n - base) / D, dim = (n - base) % D;
+  const int ld = __builtin_ctz(D);  // D = 64 or 128
+  const int head = (n - base) >> ld, dim = (n - base) & (D - 1);
   if (sect < 2 && dim >= HD) return;  // written with its rotation partner
   const bool rot = sect < 2;
   const int n2 = rot ? n + HD : n;  // the partner column (V: the column itself, unused)
-  const int64_t sstride = (int64_t)4 * 4 * NB * 64;  // f32x4 between consecutive splits
+  const int64_t sstride = (int64_t)4 * MB * NB * 64;  // f32x4 between consecutive splits
   auto first = [&](int col) {
-    const int t2 = (col >> 4) / NB, nb2 = (col >> 4) % NB;
+    const int t2 = (col >> 4) >> lnb, nb2 = (col >> 4) & (NB - 1);
     return (const f32x4*)a.partials +
-           ((((int64_t)mt * a.tiles + t2) * a.splits * 4 + wv) * 4 * NB + mb * NB + nb2) * 64 + lane;
+           ((((int64_t)mt * a.tiles + t2) * a.splits * 4 + wv) * MB * NB + mb * NB + nb2) * 64 + lane;
   };
   const f32x4* p1 = first(n);
   const f32x4* p2 = first(n2);
@@ -612,15 +620,16 @@ __global__ __launch_bounds__(256) void gemm_fixup_kernel(GemmArgs a) {
     v1 += p1[s * sstride];
     v2 += p2[s * sstride];
   }
-  // rows r0 .. r0 + 3 (those past M read row M - 1's table entries and are not stored)
+  // rows r0 .. r0 + 3 (those past M are not stored; their position is some row's of a block)
   int br[4], pos[4];
   float2 cs[4];
   float sr[4];
+  const int br0 = r0 / a.L, pos0 = r0 - br0 * a.L;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    const int r = r0 + j < a.M ? r0 + j : a.M - 1;
-    br[j] = r / a.L;
-    pos[j] = r % a.L;
+    // a block may be shorter than four rows
+    br[j] = j == 0 ? br0 : pos[j - 1] + 1 == a.L ? br[j - 1] + 1 : br[j - 1];
+    pos[j] = j == 0 ? pos0 : pos[j - 1] + 1 == a.L ? 0 : pos[j - 1] + 1;
     cs[j] = rot ? *(const float2*)(a.rope + ((int64_t)(a.P + pos[j]) * HD + dim) * 2)
                 : make_float2(1.f, 0.f);
     sr[j] = a.f8 && r0 + j < a.M ? a.sa[r0 + j] : 0.f;
@@ -663,78 +672,77 @@ __global__ __launch_bounds__(256) void gemm_fixup_kernel(GemmArgs a) {
   }
 }
 
-template <int EPI, int NB, bool F8 = false>
-hipError_t launch_nb(const GemmArgs& a, hipStream_t s) {
+template <int EPI, int NB, int MB, bool F8>
+hipError_t launch_tile(const GemmArgs& a, hipStream_t s) {
   const int grid = a.mtiles * a.gcols;
-  hipLaunchKernelGGL((gemm_kernel<EPI, NB, F8>), dim3(grid), dim3(GEMM_THREADS), 0, s, a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if constexpr (EPI == EPI_QKV) {
-    const int64_t threads = (int64_t)a.mtiles * a.tiles * 4 * 4 * NB * 64;
-    const dim3 fg((unsigned)((threads + 255) / 256));
-    switch (a.splits) {
-#define FIXUP(SC) hipLaunchKernelGGL((gemm_fixup_kernel<EPI, NB, SC>), fg, dim3(256), 0, s, a)
-      case 1: FIXUP(1); break;
-      case 2: FIXUP(2); break;
-      case 3: FIXUP(3); break;
-      case 4: FIXUP(4); break;
-      case 5: FIXUP(5); break;
-      case 6: FIXUP(6); break;
-      case 7: FIXUP(7); break;
-      case 8: FIXUP(8); break;
-      default: return hipErrorInvalidValue;  // launch_gemm admits at most QKV_MAX_SPLITS
+  hipLaunchKernelGGL((gemm_kernel<EPI, NB, MB, F8>), dim3(grid), dim3(GEMM_THREADS), 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_fixup(const GemmArgs& a, hipStream_t s) {
+  const dim3 fg((unsigned)(4 * a.mb), (unsigned)((a.N / 16 + 3) / 4), (unsigned)a.mtiles);
+  switch (a.splits) {
+#define FIXUP(SC) case SC: hipLaunchKernelGGL((gemm_fixup_kernel<SC>), fg, dim3(256), 0, s, a); break
+    FIXUP(1);
+    FIXUP(2);
+    FIXUP(3);
+    FIXUP(4);
+    FIXUP(5);
+    FIXUP(6);
+    FIXUP(7);
+    FIXUP(8);
+    default: return hipErrorInvalidValue;  // launch_gemm admits at most QKV_MAX_SPLITS
 #undef FIXUP
-    }
-    e = hipGetLastError();
   }
+  return hipGetLastError();
+}
+
+template <int EPI, int NB, bool F8>
+hipError_t launch_rows(const GemmArgs& a, hipStream_t s) {
+  hipError_t e = hipErrorInvalidValue;
+  switch (a.mb) {
+    case 1: e = launch_tile<EPI, NB, 1, F8>(a, s); break;
+    case 2: e = launch_tile<EPI, NB, 2, F8>(a, s); break;
+    case 3: e = launch_tile<EPI, NB, 3, F8>(a, s); break;
+    case 4: e = launch_tile<EPI, NB, 4, F8>(a, s); break;
+  }
+  if (EPI == EPI_QKV && e == hipSuccess) e = launch_fixup(a, s);
   return e;
 }
 
-}  // namespace
-
-int gemm_smem_bytes(int epi, int nb) {
-  switch (epi * 16 + nb) {
-    case EPI_QKV * 16 + 4: return GemmSmem<EPI_QKV, 4>::BYTES;
-    case EPI_QKV * 16 + 8: return GemmSmem<EPI_QKV, 8>::BYTES;
-    case EPI_RESID * 16 + 4: return GemmSmem<EPI_RESID, 4>::BYTES;
-    case EPI_RESID * 16 + 8: return GemmSmem<EPI_RESID, 8>::BYTES;
-    case EPI_SWIGLU * 16 + 10: return GemmSmem<EPI_SWIGLU, 10>::BYTES;
-    case EPI_LMHEAD * 16 + 8: return GemmSmem<EPI_LMHEAD, 8>::BYTES;
-    case EPI_LMHEAD * 16 + 10: return GemmSmem<EPI_LMHEAD, 10>::BYTES;
+template <bool F8>
+hipError_t launch_epi(int epi, const GemmArgs& a, hipStream_t s) {
+  switch (epi * 32 + a.nb) {
+    case EPI_QKV * 32 + 4: return launch_rows<EPI_QKV, 4, F8>(a, s);
+    case EPI_QKV * 32 + 8: return launch_rows<EPI_QKV, 8, F8>(a, s);
+    case EPI_RESID * 32 + 4: return launch_rows<EPI_RESID, 4, F8>(a, s);
+    case EPI_RESID * 32 + 8: return launch_rows<EPI_RESID, 8, F8>(a, s);
+    case EPI_SWIGLU * 32 + 4: return launch_rows<EPI_SWIGLU, 4, F8>(a, s);
+    case EPI_SWIGLU * 32 + 8: return launch_rows<EPI_SWIGLU, 8, F8>(a, s);
+    case EPI_SWIGLU * 32 + 10: return launch_rows<EPI_SWIGLU, 10, F8>(a, s);
+    case EPI_LMHEAD * 32 + 4: return launch_rows<EPI_LMHEAD, 4, F8>(a, s);
+    case EPI_LMHEAD * 32 + 8: return launch_rows<EPI_LMHEAD, 8, F8>(a, s);
+    case EPI_LMHEAD * 32 + 10: return launch_rows<EPI_LMHEAD, 10, F8>(a, s);
   }
-  return -1;
+  return hipErrorInvalidValue;
 }
+
+}  // namespace
 
 hipError_t launch_gemm(int epi, const GemmArgs& a, hipStream_t s) {
   // (epilogue, tile width) pairs the host planner may choose; splits > 1 only
   // for EPI_QKV and EPI_RESID
   if (a.splits > 1 && (epi == EPI_SWIGLU || epi == EPI_LMHEAD)) return hipErrorInvalidValue;
   if (a.KC % 4 || a.KC < 4 || a.splits < 1 || a.splits > a.KC / 4 || a.mtiles < 1 ||
-      a.gcols < 1 || a.Mp != 256 * a.mtiles)
+      a.gcols < 1 || a.mb < 1 || a.mb > 4 || a.Mp != 64 * a.mb * a.mtiles || a.M > a.Mp)
     return hipErrorInvalidValue;
-  if (a.gcols != a.tiles * a.splits) return hipErrorInvalidValue;
+  if (a.gcols != a.tiles * a.splits || a.tiles * a.nb < a.wblocks ||
+      (a.tiles - 1) * a.nb >= a.wblocks)
+    return hipErrorInvalidValue;
   if (epi == EPI_QKV && a.splits > QKV_MAX_SPLITS) return hipErrorInvalidValue;
   if (a.f8) {
     if (!a.sa || !a.sw || (epi == EPI_SWIGLU && !a.rowmax)) return hipErrorInvalidValue;
-    switch (epi * 16 + a.nb) {
-      case EPI_QKV * 16 + 4: return launch_nb<EPI_QKV, 4, true>(a, s);
-      case EPI_QKV * 16 + 8: return launch_nb<EPI_QKV, 8, true>(a, s);
-      case EPI_RESID * 16 + 4: return launch_nb<EPI_RESID, 4, true>(a, s);
-      case EPI_RESID * 16 + 8: return launch_nb<EPI_RESID, 8, true>(a, s);
-      case EPI_SWIGLU * 16 + 10: return launch_nb<EPI_SWIGLU, 10, true>(a, s);
-      case EPI_LMHEAD * 16 + 8: return launch_nb<EPI_LMHEAD, 8, true>(a, s);
-      case EPI_LMHEAD * 16 + 10: return launch_nb<EPI_LMHEAD, 10, true>(a, s);
-    }
-    return hipErrorInvalidValue;
+    return launch_epi<true>(epi, a, s);
   }
-  switch (epi * 16 + a.nb) {
-    case EPI_QKV * 16 + 4: return launch_nb<EPI_QKV, 4>(a, s);
-    case EPI_QKV * 16 + 8: return launch_nb<EPI_QKV, 8>(a, s);
-    case EPI_RESID * 16 + 4: return launch_nb<EPI_RESID, 4>(a, s);
-    case EPI_RESID * 16 + 8: return launch_nb<EPI_RESID, 8>(a, s);
-    case EPI_SWIGLU * 16 + 10: return launch_nb<EPI_SWIGLU, 10>(a, s);
-    case EPI_LMHEAD * 16 + 8: return launch_nb<EPI_LMHEAD, 8>(a, s);
-    case EPI_LMHEAD * 16 + 10: return launch_nb<EPI_LMHEAD, 10>(a, s);
-  }
-  return hipErrorInvalidValue;
+  return launch_epi<false>(epi, a, s);
 }

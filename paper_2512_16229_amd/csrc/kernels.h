@@ -47,16 +47,16 @@ hipError_t launch_window_commit(const uint16_t* staging, uint16_t* cache, const 
 
 // ------------------------------------------------------------ weight repack
 // Pack the rows of up to three [rows_i, K] bf16 sources (stacked in order) into
-// the GEMM weight layout: 16-row blocks grouped in tiles of nb blocks, stored
-// [tile][KC][nb][2][64 lanes][8] (one 1 KiB B-operand fragment per (block,
-// 64-column chunk, 32-column half)), so that one GEMM iteration streams one
-// contiguous nb x 2 KiB chunk and a tile's k-range is one contiguous run.
-// `blocks` (a multiple of nb) blocks are written; rows past the sources are
-// zero. pairs: block 2p holds rows [16p, 16p + 16) of source 0 and block 2p + 1
-// the same rows of source 1 (gate / up pairing for the SwiGLU epilogue).
+// the GEMM weight layout: 16-row blocks stored [KC][blocks][2][64 lanes][8] (one
+// 1 KiB B-operand fragment per (block, 64-column chunk, 32-column half)), so
+// that the chunk of any run of blocks is contiguous: a GEMM iteration of nb
+// blocks streams one nb x 2 KiB run, whatever nb the plan picks. `blocks` blocks
+// are written; rows past the sources are zero. pairs: block 2p holds rows
+// [16p, 16p + 16) of source 0 and block 2p + 1 the same rows of source 1 (gate /
+// up pairing for the SwiGLU epilogue).
 // K: source row length; KP (a multiple of 256, >= K): packed width, zero-filled.
 hipError_t launch_repack(const uint16_t* s0, int r0, const uint16_t* s1, int r1,
-                         const uint16_t* s2, int r2, int K, int KP, int blocks, int nb, int pairs,
+                         const uint16_t* s2, int r2, int K, int KP, int blocks, int pairs,
                          uint16_t* dst, hipStream_t s);
 hipError_t launch_bf16_to_f32(const uint16_t* src, float* dst, int n, hipStream_t s);
 // bytes [0, bytes) of device memory p set to zero by a kernel (p and bytes
@@ -64,10 +64,22 @@ hipError_t launch_bf16_to_f32(const uint16_t* src, float* dst, int n, hipStream_
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s);
 
 // ---------------------------------------------------------------- per-row
+// Padding columns of packed operands that the embedding kernel zeroes for its
+// rows: units [u0, u1) of 1 KiB per 16 rows (32 bf16 or 64 E4M3 columns) each.
+struct ZeroPad {
+  struct {
+    void* buf;
+    int u0, u1;
+  } r[2];
+  int n;
+  void add(void* buf, int u0, int u1) {
+    if (u1 > u0) r[n++] = {buf, u0, u1};
+  }
+};
 // x[r] = embed[tokens[r]] (fp32) and a[r] = pack(rmsnorm(x[r]) * w) for r < M.
 hipError_t launch_embed_norm(const int32_t* tokens, const uint16_t* embed, int vocab,
                              const float* w, float eps, int M, int Mp, int H, float* x,
-                             uint16_t* a, hipStream_t s);
+                             uint16_t* a, const ZeroPad& zp, hipStream_t s);
 // x[r] += sum over s < S of part[s][r] (row-major [S][Mp][H]; S = 0: none),
 // then a[r] = pack(rmsnorm(x[r]) * w), for r < M. H % 256 == 0.
 hipError_t launch_resnorm(const float* part, int S, const float* w, float eps, int M, int Mp,
@@ -86,11 +98,11 @@ hipError_t launch_rowscale(const uint16_t* w, int rows, int K, float* inv, float
 hipError_t launch_repack8(const uint16_t* s0, const float* inv0, const float* sc0, int r0,
                           const uint16_t* s1, const float* inv1, const float* sc1, int r1,
                           const uint16_t* s2, const float* inv2, const float* sc2, int r2, int K,
-                          int KP, int blocks, int nb, int pairs, uint8_t* dst, float* sw,
-                          hipStream_t s);
+                          int KP, int blocks, int pairs, uint8_t* dst, float* sw, hipStream_t s);
 hipError_t launch_embed_norm8(const int32_t* tokens, const uint16_t* embed, int vocab,
                               const float* w, float eps, int M, int Mp, int H, float* x,
-                              uint8_t* a8, float* sa, uint32_t* rowmax_zero, hipStream_t s);
+                              uint8_t* a8, float* sa, uint32_t* rowmax_zero, const ZeroPad& zp,
+                              hipStream_t s);
 // merge per-tile softmax partials into conf / pred
 hipError_t launch_lm_merge(const float* pm, const float* ps, const int32_t* pi, int M,
                            int tiles, float* conf, int32_t* pred, hipStream_t s);
@@ -99,17 +111,23 @@ hipError_t launch_lm_merge(const float* pm, const float* ps, const int32_t* pi, 
 enum { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_LMHEAD = 3 };
 // most k-splits of the QKV projection (its fix-up sums them with the count as a constant)
 constexpr int QKV_MAX_SPLITS = 8;
+// widest column tile in 16-column blocks: a packed weight (and its column
+// scales) is followed by this many blocks of slack, which the last tile reads
+constexpr int GEMM_MAX_NB = 10;
 
 struct GemmArgs {
   const uint16_t* A;   // packed activations, Mp rows, K columns
-  const uint16_t* W;   // packed weights [tiles][KC][nb blocks of 16 columns][2][64][8]
+  const uint16_t* W;   // packed weights [KC][wblocks blocks of 16 columns][2][64][8]; the last
+                       // tile may read GEMM_MAX_NB blocks past the end (allocated, not used)
   int M, Mp, N, KC;    // KC = K / 64 iterations per tile, a multiple of 4
   int nb;              // 16-column blocks per tile (an instantiated width)
-  int tiles;           // column tiles
+  int mb;              // 16-row blocks per wavefront, 1..4: a row tile is 64 mb rows
+  int wblocks;         // 16-column blocks of the weight
+  int tiles;           // column tiles, ceil(wblocks / nb)
   int splits;          // k-splits per tile; > 1: partial sums + fix-up kernel
-  int mtiles;          // row tiles of 256 rows; Mp = 256 * mtiles
+  int mtiles;          // row tiles of 64 mb rows; Mp = 64 * mb * mtiles
   int gcols;           // workgroups per row tile (tiles * splits when splits > 1)
-  float* partials;     // EPI_QKV: [mtiles][tiles][splits][4 waves][4][nb][64][4] fp32;
+  float* partials;     // EPI_QKV: [mtiles][tiles][splits][4 waves][mb][nb][64][4] fp32;
                        // EPI_RESID (splits > 1): row-major [splits][Mp][N] fp32, added by
                        // the following launch_resnorm (no fix-up kernel)
   // EPI_QKV
@@ -143,8 +161,6 @@ struct GemmArgs {
   uint32_t* rowmax;    // FP8 EPI_SWIGLU: atomic maximum of |output| (float bits) per row,
                        // zeroed beforehand (the requantisation's row scale)
 };
-// bytes of LDS of gemm_kernel<epi, nb> (-1: not instantiated)
-int gemm_smem_bytes(int epi, int nb);
 hipError_t launch_gemm(int epi, const GemmArgs& a, hipStream_t s);
 
 // ---------------------------------------------------------------- attention

@@ -54,7 +54,8 @@ __global__ __launch_bounds__(TPB) void resnorm_kernel(const int32_t* __restrict_
                                                       uint16_t* __restrict__ a,
                                                       uint8_t* __restrict__ a8,
                                                       float* __restrict__ sa,
-                                                      uint32_t* __restrict__ rowmax_zero) {
+                                                      uint32_t* __restrict__ rowmax_zero,
+                                                      ZeroPad zp) {
   constexpr int NW = TPB / 64;
   __shared__ float red[NW];
   __shared__ float redm[NW];
@@ -73,6 +74,11 @@ __global__ __launch_bounds__(TPB) void resnorm_kernel(const int32_t* __restrict_
     wt[i] = ((const float4*)w)[q < nq ? q : nq - 1];
   }
   if (EMBED) {
+    for (int i = 0; i < zp.n; ++i)
+      for (int q = tid; q < (zp.r[i].u1 - zp.r[i].u0) * 4; q += TPB) {
+        const int64_t unit = (int64_t)(zp.r[i].u0 + (q >> 2)) * (Mp >> 4) + (r >> 4);
+        ((uint4*)zp.r[i].buf)[unit * 64 + (r & 15) + 16 * (q & 3)] = make_uint4(0u, 0u, 0u, 0u);
+      }
     // a token outside [0, vocab) reads row 0 instead of memory past the table
     int tok = tokens[r];
     tok = (tok >= 0 && tok < vocab) ? tok : 0;
@@ -245,7 +251,7 @@ __global__ __launch_bounds__(256) void repack8_kernel(const uint16_t* __restrict
                                                       const uint16_t* __restrict__ s2,
                                                       const float* __restrict__ inv2,
                                                       const float* __restrict__ sc2, int r2,
-                                                      int K, int KC, int NB, int64_t total,
+                                                      int K, int KC, int blocks, int64_t total,
                                                       int pairs, uint8_t* __restrict__ dst,
                                                       float* __restrict__ sw) {
   const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -254,10 +260,8 @@ __global__ __launch_bounds__(256) void repack8_kernel(const uint16_t* __restrict
   int64_t u = gid >> 6;
   const int kk = (int)(u & 1);
   u >>= 1;
-  const int nbi = (int)(u % NB);
-  u /= NB;
-  const int kc = (int)(u % KC);
-  const int blk = (int)(u / KC) * NB + nbi;
+  const int kc = (int)(u % KC);  // chunks of a block in order: the source rows are read along K
+  const int blk = (int)(u / KC);
   const int k0 = kc * 128 + kk * 64 + (lane >> 4) * 16;
   const uint16_t* src = nullptr;
   float si = 0.f, sc = 0.f;
@@ -283,7 +287,8 @@ __global__ __launch_bounds__(256) void repack8_kernel(const uint16_t* __restrict
       b[e >> 2] |= f32_to_e4m3(v * si) << (8 * (e & 3));
     }
   }
-  *(uint4*)(dst + gid * 16) = make_uint4(b[0], b[1], b[2], b[3]);
+  *(uint4*)(dst + ((((int64_t)kc * blocks + blk) * 2 + kk) * 64 + lane) * 16) =
+      make_uint4(b[0], b[1], b[2], b[3]);
   if (kc == 0 && kk == 0 && (lane >> 4) == 0) sw[blk * 16 + (lane & 15)] = src ? sc : 0.f;
 }
 
@@ -350,12 +355,12 @@ __global__ __launch_bounds__(256) void lm_merge_kernel(const float* __restrict__
   }
 }
 
-// Weight repack: one thread per (fragment, lane) writes 8 bf16 (16 bytes);
-// thread order is the packed order [tile][kc][block in tile][kk][lane].
+// Weight repack: one thread per (fragment, lane) writes 8 bf16 (16 bytes) of the
+// packed order [kc][block][kk][lane].
 __global__ __launch_bounds__(256) void repack_kernel(const uint16_t* __restrict__ s0, int r0,
                                                      const uint16_t* __restrict__ s1, int r1,
                                                      const uint16_t* __restrict__ s2, int r2,
-                                                     int K, int KC, int NB, int64_t total,
+                                                     int K, int KC, int blocks, int64_t total,
                                                      int pairs, uint16_t* __restrict__ dst) {
   // K: length of a source row; KC * 64 >= K: packed columns, the excess is zero
   const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -364,10 +369,8 @@ __global__ __launch_bounds__(256) void repack_kernel(const uint16_t* __restrict_
   int64_t u = gid >> 6;
   const int kk = (int)(u & 1);
   u >>= 1;
-  const int nbi = (int)(u % NB);
-  u /= NB;
-  const int kc = (int)(u % KC);
-  const int blk = (int)(u / KC) * NB + nbi;
+  const int kc = (int)(u % KC);  // chunks of a block in order: the source rows are read along K
+  const int blk = (int)(u / KC);
   const int k0 = kc * 64 + kk * 32 + (lane >> 4) * 8;
   const uint16_t* src = nullptr;
   int row = 0;
@@ -383,7 +386,7 @@ __global__ __launch_bounds__(256) void repack_kernel(const uint16_t* __restrict_
   }
   uint4 v = make_uint4(0, 0, 0, 0);
   if (src && k0 < K) v = *(const uint4*)(src + (int64_t)row * K + k0);
-  *(uint4*)(dst + gid * 8) = v;
+  *(uint4*)(dst + ((((int64_t)kc * blocks + blk) * 2 + kk) * 64 + lane) * 8) = v;
 }
 
 __global__ void bf16_to_f32_kernel(const uint16_t* __restrict__ s, float* __restrict__ d, int n) {
@@ -400,12 +403,12 @@ int resnorm_shape(int H) { return H <= 1024 ? 1 : H <= 2048 ? 2 : H <= 4096 ? 3 
 
 hipError_t launch_embed_norm(const int32_t* tokens, const uint16_t* embed, int vocab,
                              const float* w, float eps, int M, int Mp, int H, float* x,
-                             uint16_t* a, hipStream_t s) {
+                             uint16_t* a, const ZeroPad& zp, hipStream_t s) {
   if (H % 256 || H > H_MAX) return hipErrorInvalidValue;
 #define EMBEDNORM(NG, TPB)                                                                \
   hipLaunchKernelGGL((resnorm_kernel<true, 0, NG, false, TPB>), dim3(M), dim3(TPB), 0, s,      \
                      tokens, embed, vocab, nullptr, 0, w, eps, M, Mp, H, x, a, nullptr, nullptr, \
-                     nullptr)
+                     nullptr, zp)
   switch (resnorm_shape(H)) {
     case 1: EMBEDNORM(1, 256); break;
     case 2: EMBEDNORM(1, 512); break;
@@ -418,11 +421,12 @@ hipError_t launch_embed_norm(const int32_t* tokens, const uint16_t* embed, int v
 
 hipError_t launch_embed_norm8(const int32_t* tokens, const uint16_t* embed, int vocab,
                               const float* w, float eps, int M, int Mp, int H, float* x,
-                              uint8_t* a8, float* sa, uint32_t* rz, hipStream_t s) {
+                              uint8_t* a8, float* sa, uint32_t* rz, const ZeroPad& zp,
+                              hipStream_t s) {
   if (H % 256 || H > H_MAX || !a8 || !sa) return hipErrorInvalidValue;
 #define EMBEDNORM8(NG, TPB)                                                               \
   hipLaunchKernelGGL((resnorm_kernel<true, 0, NG, true, TPB>), dim3(M), dim3(TPB), 0, s,       \
-                     tokens, embed, vocab, nullptr, 0, w, eps, M, Mp, H, x, nullptr, a8, sa, rz)
+                     tokens, embed, vocab, nullptr, 0, w, eps, M, Mp, H, x, nullptr, a8, sa, rz, zp)
   switch (resnorm_shape(H)) {
     case 1: EMBEDNORM8(1, 256); break;
     case 2: EMBEDNORM8(1, 512); break;
@@ -439,7 +443,7 @@ void resnorm_ng(const float* part, int S, const float* w, float eps, int M, int 
                 float* x, uint16_t* a, uint8_t* a8, float* sa, uint32_t* rz, hipStream_t s) {
 #define RESNORM(SC)                                                                         \
   hipLaunchKernelGGL((resnorm_kernel<false, SC, NG, A8, TPB>), dim3(M), dim3(TPB), 0, s, nullptr, \
-                     nullptr, 0, part, S, w, eps, M, Mp, H, x, a, a8, sa, rz)
+                     nullptr, 0, part, S, w, eps, M, Mp, H, x, a, a8, sa, rz, ZeroPad{})
   switch (S) {
     case 0: RESNORM(0); break;
     case 2: RESNORM(2); break;
@@ -499,13 +503,12 @@ hipError_t launch_rowscale(const uint16_t* w, int rows, int K, float* inv, float
 hipError_t launch_repack8(const uint16_t* s0, const float* inv0, const float* sc0, int r0,
                           const uint16_t* s1, const float* inv1, const float* sc1, int r1,
                           const uint16_t* s2, const float* inv2, const float* sc2, int r2, int K,
-                          int KP, int blocks, int nb, int pairs, uint8_t* dst, float* sw,
-                          hipStream_t s) {
-  if (KP % 512 || KP < K || K % 16 || nb < 1 || blocks % nb) return hipErrorInvalidValue;
+                          int KP, int blocks, int pairs, uint8_t* dst, float* sw, hipStream_t s) {
+  if (KP % 512 || KP < K || K % 16 || blocks < 1) return hipErrorInvalidValue;
   const int KC = KP / 128;
   const int64_t total = (int64_t)blocks * KC * 2 * 64;
   hipLaunchKernelGGL(repack8_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, s0,
-                     inv0, sc0, r0, s1, inv1, sc1, r1, s2, inv2, sc2, r2, K, KC, nb, total, pairs,
+                     inv0, sc0, r0, s1, inv1, sc1, r1, s2, inv2, sc2, r2, K, KC, blocks, total, pairs,
                      dst, sw);
   return hipGetLastError();
 }
@@ -517,14 +520,14 @@ hipError_t launch_lm_merge(const float* pm, const float* ps, const int32_t* pi, 
 }
 
 hipError_t launch_repack(const uint16_t* s0, int r0, const uint16_t* s1, int r1,
-                         const uint16_t* s2, int r2, int K, int KP, int blocks, int nb, int pairs,
+                         const uint16_t* s2, int r2, int K, int KP, int blocks, int pairs,
                          uint16_t* dst, hipStream_t s) {
-  if (KP % 256 || KP < K || nb < 1 || blocks % nb) return hipErrorInvalidValue;
+  if (KP % 256 || KP < K || blocks < 1) return hipErrorInvalidValue;
   const int KC = KP / 64;
   const int64_t total = (int64_t)blocks * KC * 2 * 64;
   const int64_t grid = (total + 255) / 256;
   hipLaunchKernelGGL(repack_kernel, dim3((unsigned)grid), dim3(256), 0, s, s0, r0, s1, r1, s2,
-                     r2, K, KC, nb, total, pairs, dst);
+                     r2, K, KC, blocks, total, pairs, dst);
   return hipGetLastError();
 }
 

@@ -88,6 +88,28 @@ def test_long_prefix_attention(cfgname, P, L, k):
     check_forward(s, bt, conf, pred, label=f"prefix {P}")
 
 
+# rows at and around every row tile of the GEMMs (64 mb rows, mb 1..4, and two
+# tiles: 257 rows take 2 x 192, 399 rows 2 x 256), padding rows included
+ROW_TILES = [(1, 64, "bf16"), (5, 13, "bf16"), (2, 64, "fp8"), (3, 43, "fp8"), (3, 64, "bf16"),
+             (4, 49, "bf16"), (9, 29, "fp8"), (7, 57, "bf16")]
+
+
+@pytest.mark.parametrize("nb,L,prec", ROW_TILES)
+def test_row_tiles(nb, L, prec):
+    log(f"row tiles {nb} x {L} {prec}")
+    s = Setup("small", 33, L, nb - 1, precision=prec)
+    s.load_oracle_cache()
+    mask = s.cfg["mask_id"]
+    rng = np.random.default_rng(nb * L)
+    # a larger forward first: the operand buffers hold its rows and columns
+    big = np.full((nb, L), 7)
+    s.gpu_forward(big)
+    bt = np.where(rng.random((nb, L)) < 0.7, mask, rng.integers(0, s.cfg["vocab"] - 1, (nb, L)))
+    for n in (nb, 1):
+        conf, pred = s.gpu_forward(bt[:n])
+        check_forward(s, bt[:n], conf, pred, label=f"{n} x {L}")
+
+
 @pytest.mark.parametrize("cfgname,P,L,k", [("tiny", 64, 16, 3), ("small", 100, 32, 7),
                                            ("small128", 40, 16, 1)])
 def test_hidden_states_per_layer(cfgname, P, L, k):
