@@ -208,6 +208,21 @@ int lopa_verify_forward(const lopa_model* m, lopa_kv* kv, int32_t prefix_len,
                         const int32_t* branch_tokens, int32_t n_branches, int32_t L,
                         float* conf, int32_t* pred, void* stream);
 
+/* Prompt encoding, block-causal in blocks of `block` (Sec. 3.4): the post-RoPE K
+ * and V of tokens[n_tokens] go to the cache positions prefix_len ..
+ * prefix_len + n_tokens - 1; a token sees the cache up to the end of its own
+ * block. The result is that of encoding block after block with
+ * lopa_verify_forward (one branch) and lopa_commit_kv, but runs of blocks, as many
+ * rows as the lopa_kv's working buffers hold (max_branches * max_block, 256 at
+ * least), go through the layers together, and nothing is computed past the last
+ * layer's K and V. Afterwards the lopa_kv is as after the last block's forward
+ * (its K and V are staging branch 0). LOPA_ESHAPE: a block (the shorter of `block`
+ * and n_tokens) exceeds max_block; LOPA_ECAPACITY: prefix_len + n_tokens >
+ * max_len; LOPA_EINVAL: a block exceeds the sub-block set by
+ * lopa_kv_set_block_causal. */
+int lopa_prefill(const lopa_model* m, lopa_kv* kv, int32_t prefix_len, const int32_t* tokens,
+                 int32_t n_tokens, int32_t block, void* stream);
+
 /* Eq. 2 and Alg. 1 step 3 selection; Sec. 3.2 logit reuse.
  * In:  branch_tokens[n_branches*L], conf/pred[n_branches*L] from
  *      lopa_verify_forward on those branches, valid[n_branches].

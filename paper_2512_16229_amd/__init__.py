@@ -96,6 +96,7 @@ class KV:
         _check(lib.lopa_kv_create(model.handle, max_len, max_branches, max_block, C.byref(h)))
         self.handle, self.model = h, model
         self.max_len, self.max_branches, self.max_block = max_len, max_branches, max_block
+        self.block_causal = 0
 
     def read(self, layer: int, start: int, length: int, stream=None):
         c = self.model.cfg
@@ -120,6 +121,7 @@ class KV:
         """0: full attention inside the block; c > 0 (multiple of 16): rows of
         sub-block b see the prefix and sub-blocks 0..b of their branch."""
         _check(lib.lopa_kv_set_block_causal(self.handle, sub_block))
+        self.block_causal = sub_block
 
     def profile(self, kinds=()):
         """Time launches of the given kinds (names from PROF_KINDS) with HIP events."""
@@ -173,6 +175,11 @@ def lopa_verify_forward(model: Model, kv: KV, prefix_len, branch_tokens, n_branc
                                    _ptr(branch_tokens, I32, "branch_tokens"), n_branches, L,
                                    _ptr(conf, F32, "conf"), _ptr(pred, I32, "pred"),
                                    _stream(stream)))
+
+
+def lopa_prefill(model: Model, kv: KV, prefix_len, tokens, block, stream=None):
+    _check(lib.lopa_prefill(model.handle, kv.handle, prefix_len, _ptr(tokens, I32, "tokens"),
+                            tokens.numel(), block, _stream(stream)))
 
 
 def lopa_verify_forward_noalloc(model: Model, kv: KV, prefix_len, branch_tokens, n_branches, L,

@@ -48,7 +48,7 @@ class lopa_weight_ptrs(C.Structure):
 
 EXPORTS = ["lopa_model_create", "lopa_model_create_ex", "lopa_model_destroy", "lopa_kv_create", "lopa_kv_destroy",
            "lopa_strerror", "lopa_last_error", "lopa_build_branches", "lopa_build_branches_window",
-           "lopa_verify_forward",
+           "lopa_verify_forward", "lopa_prefill",
            "lopa_branch_confidence_select", "lopa_branch_confidence_select_metric", "lopa_commit_kv",
            "lopa_commit_kv_rows", "lopa_kv_read", "lopa_kv_write",
            "lopa_kv_read_staging", "lopa_debug_hidden",
@@ -78,6 +78,7 @@ def _load():
         "lopa_build_branches": (C.c_int, [P, P, P, I32, I32, F32, I32, P, P, P, P, P]),
         "lopa_build_branches_window": (C.c_int, [P, P, P, I32, I32, I32, F32, I32, P, P, P, P, P]),
         "lopa_verify_forward": (C.c_int, [P, P, I32, P, I32, I32, P, P, P]),
+        "lopa_prefill": (C.c_int, [P, P, I32, P, I32, I32, P]),
         "lopa_branch_confidence_select": (C.c_int, [P, P, P, P, I32, I32, I32, P, P, P, P, P, P, P]),
         "lopa_branch_confidence_select_metric": (C.c_int, [P, P, P, P, I32, I32, I32, I32, I32, F32,
                                                            P, P, P, P, P, P, P]),

@@ -55,7 +55,7 @@ int dalloc(DevBuf& b, size_t bytes, std::vector<void*>& owned) {
 }
 
 // Packed weights: [K / 64][blocks of 16 output features][2][64][8] bf16 (E4M3:
-// [K / 128][blocks][2][64][16]), followed by GEMM_MAX_NB blocks of zeros.
+// [K / 128][blocks][2][64][16]), followed by GEMM_MAX_NB blocks of slack.
 struct LayerPack {
   uint16_t* qkv;   // blk_qkv blocks, K = H (models with a bf16 QKV projection)
   uint16_t* o;     // blk_h blocks, K = Hq * d
@@ -189,8 +189,11 @@ struct StepPlans {
 
 struct lopa_kv {
   const lopa_model* m = nullptr;
-  std::vector<StepPlans> plans;  // by row count, up to max_branches * max_block
-  int max_len = 0, max_branches = 0, max_block = 0, mp_max = 0;
+  std::vector<StepPlans> plans;  // by row count, up to ws_rows
+  int max_len = 0, max_branches = 0, max_block = 0;
+  int ws_rows = 0;              // rows the working buffers hold (plans, qbuf): a forward's
+                                // max_branches * max_block, 256 at least (prompt encoding)
+  int mp_max = 0;               // ws_rows in whole 256-row tiles
   int vld = 0, vlds = 0;        // positions per head region: max_len, max_block rounded up to 32
   uint16_t* cache = nullptr;    // [layers][2][Hkv][d * vld], KV tile layout (common.h)
   uint16_t* staging = nullptr;  // [max_branches][layers][2][Hkv][d * vlds]
@@ -437,29 +440,20 @@ int lopa_model_create_ex(const lopa_model_cfg* cfg, const lopa_weight_ptrs* w, i
   const int FP = round256(F);  // down projection K, zero-padded
   const int KPH8 = round512(H), KPF8 = round512(F);  // FP8 MLP K, zero-padded
   // elements of a packed weight: blocks x K x 16 (without its slack, see
-  // GEMM_MAX_NB); columns of its scales
+  // GEMM_MAX_NB)
   auto wsize = [](int blocks, int K) { return (size_t)blocks * K * 16; };
-  auto ncols = [](int blocks) { return (size_t)(blocks + GEMM_MAX_NB) * 16; };
-  // packed weights with their slack, whose last GEMM_MAX_NB blocks are zeroed
+  // packed weights with their slack: read by a projection's last tile, whatever
+  // it holds only reaches columns that no epilogue stores or counts
   constexpr size_t SLACK = (size_t)GEMM_MAX_NB * 2048;
   auto allocw = [&](void** p, size_t bytes) -> int {
     DevBuf b;
     int r = dalloc(b, bytes + SLACK, m->owned);
     *p = b.p;
-    if (!r && launch_fill_zero((char*)b.p + bytes, SLACK, s) != hipSuccess)
-      r = fail(LOPA_EHIP, "clearing a weight's slack failed");
     return r;
   };
   auto allocw16 = [&](uint16_t** p, size_t elems) { return allocw((void**)p, elems * 2); };
   auto allocw8 = [&](uint8_t** p, size_t bytes) { return allocw((void**)p, bytes); };
-  auto allocs = [&](float** p, int blocks) -> int {
-    DevBuf b;
-    int r = dalloc(b, ncols(blocks) * 4, m->owned);
-    *p = (float*)b.p;
-    if (!r && launch_fill_zero(b.p, ncols(blocks) * 4, s) != hipSuccess)
-      r = fail(LOPA_EHIP, "clearing the column scales failed");
-    return r;
-  };
+  auto allocs = [&](float** p, int blocks) { return allocf(p, (size_t)(blocks + GEMM_MAX_NB) * 16); };
   // FP8: per source row scaling pairs (gate, up: F rows; down: H rows; q, k,
   // v: n_qkv rows; LM head: V rows)
   float *inv_g = nullptr, *sc_g = nullptr, *inv_u = nullptr, *sc_u = nullptr, *inv_d = nullptr,
@@ -584,7 +578,8 @@ int lopa_kv_create(const lopa_model* m, int32_t max_len, int32_t max_branches, i
   kv->max_len = max_len;
   kv->max_branches = max_branches;
   kv->max_block = max_block;
-  kv->mp_max = padded_rows(max_branches * max_block);
+  kv->ws_rows = std::max(256, max_branches * max_block);
+  kv->mp_max = padded_rows(kv->ws_rows);
   const int H = c.hidden, F = c.ffn, d = c.head_dim, Hkv = c.kv_heads;
   auto bail = [&](int code) {
     delete kv;
@@ -598,8 +593,8 @@ int lopa_kv_create(const lopa_model* m, int32_t max_len, int32_t max_branches, i
   const size_t stag_e = (size_t)max_branches * c.layers * 2 * Hkv * d * kv->vlds;
   size_t part_b = 16;
   size_t lm_n = 0;
-  kv->plans = all_plans(m, max_branches * max_block);
-  for (int M = 1; M <= max_branches * max_block; ++M) {
+  kv->plans = all_plans(m, kv->ws_rows);
+  for (int M = 1; M <= kv->ws_rows; ++M) {
     const StepPlans& p = kv->plans[M];
     part_b = std::max(part_b, partial_bytes(m, p));
     lm_n = std::max(lm_n, lm_stats(p));
@@ -628,7 +623,7 @@ int lopa_kv_create(const lopa_model* m, int32_t max_len, int32_t max_branches, i
     KV_ALLOC(sa_dn, float*, rows * 4);
     KV_ALLOC(rowmax_dn, uint32_t*, rows * 4);
   }
-  KV_ALLOC(qbuf, uint16_t*, (size_t)max_branches * c.heads * max_block * d * 2);
+  KV_ALLOC(qbuf, uint16_t*, (size_t)kv->ws_rows * c.heads * d * 2);
   KV_ALLOC(partials, float*, part_b);
   KV_ALLOC(pm, float*, lm_n * 4);
   KV_ALLOC(ps, float*, lm_n * 4);
@@ -686,13 +681,18 @@ int lopa_build_branches(const int32_t* tokens, const float* conf, const int32_t*
 
 // The verify forward; with stop_layer >= 0 it stops after that many layers and
 // copies the fp32 residual stream to x_out instead of producing conf / pred.
+// chain_rows > 0: the rows are chain_rows consecutive tokens of one sequence in
+// n_branches blocks of L (the last may be short) whose K / V go to the cache from
+// prefix_len on, each block seeing the cache up to its own end; the forward ends
+// with the last layer's K / V (nothing after them is asked for). stage_last: the
+// last block's K / V also go to staging branch 0.
 static int verify_impl(const lopa_model* m, lopa_kv* kv, int32_t prefix_len,
                        const int32_t* branch_tokens, int32_t n_branches, int32_t L, float* conf,
                        int32_t* pred, void* stream, int stop_layer, float* x_out,
-                       const VerifyWs& ws) {
+                       const VerifyWs& ws, int chain_rows = 0, bool stage_last = false) {
   const lopa_model_cfg& c = m->cfg;
   hipStream_t s = (hipStream_t)stream;
-  const int M = n_branches * L;
+  const int M = chain_rows ? chain_rows : n_branches * L;
   const int H = c.hidden, F = c.ffn, d = c.head_dim;
   const StepPlans& plan = kv->plans[M];
   const int Mp = plan.rt.rows();
@@ -770,9 +770,10 @@ static int verify_impl(const lopa_model* m, lopa_kv* kv, int32_t prefix_len,
   at.layers = c.layers;
   at.vlds = kv->vlds;
   at.Mp = Mp;
+  at.chain_rows = chain_rows;
   at.scale = 1.0f / std::sqrt((float)d);
   // a block of one sub-block (or less) needs no mask
-  at.cblk = kv->causal_blk && L > kv->causal_blk ? kv->causal_blk : 0;
+  at.cblk = !chain_rows && kv->causal_blk && L > kv->causal_blk ? kv->causal_blk : 0;
   at.scratch = ws.partials;
   at.scratch_bytes = ws.partials_bytes;
   // FP8 output projection: the attention output's row maxima, in the buffer
@@ -794,15 +795,23 @@ static int verify_impl(const lopa_model* m, lopa_kv* kv, int32_t prefix_len,
     g.L = L;
     g.vlds = kv->vlds;
     g.P = prefix_len;
+    uint16_t* kc = kv->cache + ((size_t)l * 2 + 0) * c.kv_heads * d * kv->vld;
+    uint16_t* vc = kv->cache + ((size_t)l * 2 + 1) * c.kv_heads * d * kv->vld;
+    g.chain = chain_rows > 0;
+    g.stage_block = stage_last ? n_branches - 1 : -1;
+    g.vld = kv->vld;
+    g.kcache = kc;
+    g.vcache = vc;
     { ProfScope ps_(kv, LOPA_PROF_QKV, s);
       if (f8x)
         HIP_TRY(gemm8(EPI_QKV, ws.a8_gu, p.qkv8, m->n_qkv, round512(H), ws.sa_gu, p.sw_qkv,
                       plan.qkv));
       else
         HIP_TRY(gemm(EPI_QKV, ws.abuf, p.qkv, m->n_qkv, H, plan.qkv)); }
+    if (chain_rows && l + 1 == c.layers) return LOPA_OK;
     at.layer = l;
-    at.kcache = kv->cache + ((size_t)l * 2 + 0) * c.kv_heads * d * kv->vld;
-    at.vcache = kv->cache + ((size_t)l * 2 + 1) * c.kv_heads * d * kv->vld;
+    at.kcache = kc;
+    at.vcache = vc;
     { ProfScope ps_(kv, LOPA_PROF_ATTN, s);
       HIP_TRY(launch_attention(at, s)); }
     g.x = ws.x;
@@ -923,6 +932,38 @@ int lopa_verify_forward(const lopa_model* m, lopa_kv* kv, int32_t prefix_len,
   if (rc) return rc;
   return verify_impl(m, kv, prefix_len, branch_tokens, n_branches, L, conf, pred, stream, -1,
                      nullptr, kv_ws(kv));
+}
+
+int lopa_prefill(const lopa_model* m, lopa_kv* kv, int32_t prefix_len, const int32_t* tokens,
+                 int32_t n_tokens, int32_t block, void* stream) {
+  if (!m || !kv || !tokens) return fail(LOPA_EINVAL, "null pointer argument");
+  if (kv->m != m) return fail(LOPA_EINVAL, "kv was created for another model");
+  if (n_tokens < 1 || block < 1) return fail(LOPA_ESHAPE, "n_tokens and block must be >= 1");
+  const int L = std::min(block, n_tokens);
+  if (L > kv->max_block)
+    return fail(LOPA_ESHAPE, "blocks of %d exceed kv capacity %d", L, kv->max_block);
+  if (prefix_len < 0) return fail(LOPA_EINVAL, "prefix_len < 0");
+  if ((int64_t)prefix_len + n_tokens > kv->max_len)
+    return fail(LOPA_ECAPACITY, "prefix_len %d + %d tokens > max_len %d", prefix_len, n_tokens,
+                kv->max_len);
+  if (kv->causal_blk && L > kv->causal_blk)
+    return fail(LOPA_EINVAL, "blocks of %d are longer than the block-causal sub-block %d", L,
+                kv->causal_blk);
+  // runs of whole blocks as large as the working buffers
+  const int run = kv->ws_rows / L * L;
+  for (int pos = 0; pos < n_tokens; pos += run) {
+    const int M = std::min(run, n_tokens - pos), nb = (M + L - 1) / L;
+    const bool last = pos + M == n_tokens;
+    int rc = verify_impl(m, kv, prefix_len + pos, tokens + pos, nb, L, nullptr, nullptr, stream, -1,
+                         nullptr, kv_ws(kv), M, last);
+    if (rc) return rc;
+    if (last) {  // as after a forward and commit of the last block alone
+      kv->last_nb = 1;
+      kv->last_L = M - (nb - 1) * L;
+      kv->last_P = prefix_len + pos + (nb - 1) * L;
+    }
+  }
+  return LOPA_OK;
 }
 
 int lopa_debug_hidden(const lopa_model* m, lopa_kv* kv, int32_t prefix_len,

@@ -31,6 +31,19 @@ namespace {
 
 constexpr int KT = 32;  // keys per tile
 
+// What the rows of branch br see: P cache positions, then Lk keys of their own
+// staging; Lr rows. Chained (AttnArgs::chain_rows): branch br is block br of a
+// run of blocks whose K / V are in the cache already, and sees the cache up to
+// its own end; the last block may be short.
+struct AttnSpan {
+  int P, Lk, Lr;
+};
+__host__ __device__ __forceinline__ AttnSpan attn_span(const AttnArgs& a, int br) {
+  if (!a.chain_rows) return {a.P, a.L, a.L};
+  const int r0 = br * a.L, left = a.chain_rows - r0, Lr = left < a.L ? left : a.L;
+  return {a.P + r0 + Lr, 0, Lr};
+}
+
 template <int D>
 struct AttnTile {
   u32x4 k[2][D / 32];  // K fragments (kb, kk) in the KV tile layout
@@ -250,8 +263,9 @@ __global__ __launch_bounds__(256) void attn_kernel(AttnArgs a) {
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 4, c16 = lane & 15;
   const int kvh = h / (a.Hq / a.Hkv);
-  const int L = a.L, P = a.P;
-  const int pt = (P + KT - 1) / KT, bt = (L + KT - 1) / KT, T = pt + bt;
+  const AttnSpan span = attn_span(a, br);
+  const int L = a.L, P = span.P, Lk = span.Lk, Lr = span.Lr;
+  const int pt = (P + KT - 1) / KT, bt = (Lk + KT - 1) / KT, T = pt + bt;
   const int t_lo = wv * T / 4, t_hi = (wv + 1) * T / 4;
   const float sl2 = a.scale * 1.4426950408889634f;  // scale * log2(e)
 
@@ -295,8 +309,8 @@ __global__ __launch_bounds__(256) void attn_kernel(AttnArgs a) {
 #pragma unroll
   for (int qb = 0; qb < QB; ++qb) {
     const int row = row0 + qb * 16 + c16;
-    const uint16_t* qrow = a.q + (((int64_t)br * a.Hq + h) * L + (row < L ? row : 0)) * D;
-    const unsigned keep = row < L ? ~0u : 0u;  // rows past L: zero queries
+    const uint16_t* qrow = a.q + (((int64_t)br * a.Hq + h) * L + (row < Lr ? row : 0)) * D;
+    const unsigned keep = row < Lr ? ~0u : 0u;  // rows past the block: zero queries
 #pragma unroll
     for (int kk = 0; kk < NKK; ++kk) qf[qb][kk] = *(const u32x4*)(qrow + kk * 32 + g * 8) & keep;
   }
@@ -312,7 +326,7 @@ __global__ __launch_bounds__(256) void attn_kernel(AttnArgs a) {
     const int t = tile_of(i);
     const bool pre = t < pt;
     tile_max<D, QB>(smem + (wv * 2 + (i & 1)) * TileLds<D>::TILE, lane, qf, mraw,
-                    (pre ? t : t - pt) * KT, pre ? P : L, g, pre ? 0 : a.cblk, row0);
+                    (pre ? t : t - pt) * KT, pre ? P : Lk, g, pre ? 0 : a.cblk, row0);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     issue_k(tile_of(i + 2 < n ? i + 2 : n - 1), i & 1);
   }
@@ -352,7 +366,7 @@ __global__ __launch_bounds__(256) void attn_kernel(AttnArgs a) {
     tile_fetch<D>(smem + (wv * 2 + (i & 1)) * TileLds<D>::TILE, lane, x);
     const int t = tile_of(i);
     const bool pre = t < pt;
-    tile_update<D, QB, false>(x, qf, m, l, o, (pre ? t : t - pt) * KT, pre ? P : L, sl2, g,
+    tile_update<D, QB, false>(x, qf, m, l, o, (pre ? t : t - pt) * KT, pre ? P : Lk, sl2, g,
                               pre ? 0 : a.cblk, row0);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     issue(tile_of(i + 2 < n ? i + 2 : n - 1), i & 1);
@@ -397,7 +411,7 @@ __global__ __launch_bounds__(256) void attn_kernel(AttnArgs a) {
 #pragma unroll
   for (int qb = 0; qb < QB; ++qb) {
     const int row = row0 + qb * 16 + c16;
-    const bool ok = row < L;
+    const bool ok = row < Lr;
     const float inv = ok ? 1.0f / l[qb] : 0.f;
     const int r = br * L + row;
     float mrow = 0.f;  // largest |stored value| of this lane's part of the row
@@ -454,8 +468,9 @@ __global__ __launch_bounds__(64 * SL_WAVES) void attn_sl_kernel(AttnArgs a) {
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 4, c16 = lane & 15;
   const int kvh = h / (a.Hq / a.Hkv);
-  const int L = a.L, P = a.P;
-  const int pt = (P + KT - 1) / KT, bt = (L + KT - 1) / KT, T = pt + bt;
+  const AttnSpan span = attn_span(a, br);
+  const int L = a.L, P = span.P, Lk = span.Lk, Lr = span.Lr;
+  const int pt = (P + KT - 1) / KT, bt = (Lk + KT - 1) / KT, T = pt + bt;
   const int t_lo = wv * T / SL_WAVES, nt = (wv + 1) * T / SL_WAVES - t_lo;  // nt <= NT
   const float sl2 = a.scale * 1.4426950408889634f;
 
@@ -484,8 +499,8 @@ __global__ __launch_bounds__(64 * SL_WAVES) void attn_sl_kernel(AttnArgs a) {
 #pragma unroll
   for (int qb = 0; qb < QB; ++qb) {
     const int row = qb * 16 + c16;
-    const uint16_t* qrow = a.q + (((int64_t)br * a.Hq + h) * L + (row < L ? row : 0)) * D;
-    const unsigned keep = row < L ? ~0u : 0u;  // rows past L: zero queries
+    const uint16_t* qrow = a.q + (((int64_t)br * a.Hq + h) * L + (row < Lr ? row : 0)) * D;
+    const unsigned keep = row < Lr ? ~0u : 0u;  // rows past the block: zero queries
 #pragma unroll
     for (int kk = 0; kk < NKK; ++kk) qf[qb][kk] = *(const u32x4*)(qrow + kk * 32 + g * 8) & keep;
   }
@@ -501,7 +516,7 @@ __global__ __launch_bounds__(64 * SL_WAVES) void attn_sl_kernel(AttnArgs a) {
     if (i >= nt) break;
     const int t = t_lo + i;
     const bool pre = t < pt;
-    const int p0 = (pre ? t : t - pt) * KT, lim = pre ? P : L;
+    const int p0 = (pre ? t : t - pt) * KT, lim = pre ? P : Lk;
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
       int lq = lim;  // block-causal: rows 16 qb .. lie in one sub-block
@@ -561,7 +576,7 @@ __global__ __launch_bounds__(64 * SL_WAVES) void attn_sl_kernel(AttnArgs a) {
     if (i >= nt) break;
     const int t = t_lo + i;
     const bool pre = t < pt;
-    const int p0 = (pre ? t : t - pt) * KT, lim = pre ? P : L;
+    const int p0 = (pre ? t : t - pt) * KT, lim = pre ? P : Lk;
     if (p0 + KT > lim) {
       // zero V at keys past the end of the source (0 * inf would poison o)
 #pragma unroll
@@ -608,7 +623,7 @@ __global__ __launch_bounds__(64 * SL_WAVES) void attn_sl_kernel(AttnArgs a) {
     const int ln = f & 63, qb = (f >> 6) % QB, db = (f >> 6) / QB;
     const int q16 = ln & 15, g4 = ln >> 4;
     const int row = qb * 16 + q16;
-    if (row >= L) continue;
+    if (row >= Lr) continue;
     f32x4 acc = s_o[0][f];
     float ls = s_l[0][qb * 16 + q16];
 #pragma unroll
@@ -640,7 +655,7 @@ __global__ __launch_bounds__(64 * SL_WAVES) void attn_sl_kernel(AttnArgs a) {
       const int qb = tid >> 4, row = qb * 16 + (tid & 15);
       float m = 0.f;
       for (int w = qb; w < SL_WAVES; w += QB) m = fmaxf(m, s_m[w * 16 + (tid & 15)]);
-      if (row < L) atomicMax(a.rowmax + br * L + row, __float_as_uint(m));
+      if (row < Lr) atomicMax(a.rowmax + br * L + row, __float_as_uint(m));
     }
   }
 }
@@ -701,13 +716,13 @@ __device__ __forceinline__ void group_issue(const AttnArgs& a, const GroupSplit&
 
 // Q^T operand of query head h, rows 16 qb + c16 of branch br (zero past L)
 template <int D, int QB>
-__device__ __forceinline__ void group_q(const AttnArgs& a, int br, int h, int c16, int g,
+__device__ __forceinline__ void group_q(const AttnArgs& a, int br, int Lr, int h, int c16, int g,
                                         u32x4 (&qf)[QB][D / 32]) {
 #pragma unroll
   for (int qb = 0; qb < QB; ++qb) {
     const int row = qb * 16 + c16;
-    const uint16_t* qrow = a.q + (((int64_t)br * a.Hq + h) * a.L + (row < a.L ? row : 0)) * D;
-    const unsigned keep = row < a.L ? ~0u : 0u;
+    const uint16_t* qrow = a.q + (((int64_t)br * a.Hq + h) * a.L + (row < Lr ? row : 0)) * D;
+    const unsigned keep = row < Lr ? ~0u : 0u;
 #pragma unroll
     for (int kk = 0; kk < D / 32; ++kk)
       qf[qb][kk] = *(const u32x4*)(qrow + kk * 32 + g * 8) & keep;
@@ -736,7 +751,8 @@ __global__ __launch_bounds__(512) void attn_gmax_kernel(AttnArgs a, int NS) {
   const int G = a.Hq / a.Hkv;
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int h = kvh * G + wv, g = lane >> 4, c16 = lane & 15;
-  const GroupSplit gs = group_split(a.P, a.L, sp, NS);
+  const AttnSpan span = attn_span(a, br);
+  const GroupSplit gs = group_split(span.P, span.Lk, sp, NS);
   const int np = gs.np;
   const uint16_t* kc = a.kcache + (int64_t)kvh * D * a.vld;
   const uint16_t* vc = a.vcache + (int64_t)kvh * D * a.vld;
@@ -749,7 +765,7 @@ __global__ __launch_bounds__(512) void attn_gmax_kernel(AttnArgs a, int NS) {
     for (int i = 0; i < GQ_RING - 1; ++i)
       group_issue<D, QB, false>(a, gs, i, i, ring, kc, vc, ks, vs, lane);
   u32x4 qf[QB][D / 32];
-  group_q<D, QB>(a, br, h, c16, g, qf);
+  group_q<D, QB>(a, br, span.Lr, h, c16, g, qf);
   float mraw[QB];
 #pragma unroll
   for (int qb = 0; qb < QB; ++qb) mraw[qb] = -INFINITY;
@@ -761,7 +777,7 @@ __global__ __launch_bounds__(512) void attn_gmax_kernel(AttnArgs a, int NS) {
                                 ks, vs, lane);
     const bool pre = i < np;
     tile_max<D, QB>(smem + (i % GQ_RING) * T::KBYTES, lane, qf, mraw,
-                    (pre ? gs.p_lo + i : i - np) * KT, pre ? a.P : a.L, g, pre ? 0 : a.cblk, 0);
+                    (pre ? gs.p_lo + i : i - np) * KT, pre ? span.P : span.Lk, g, pre ? 0 : a.cblk, 0);
   }
   if (wv == 0) attn_wait_vmcnt<0>();
   const GroupScratch sc = group_scratch(a, NS);
@@ -769,7 +785,7 @@ __global__ __launch_bounds__(512) void attn_gmax_kernel(AttnArgs a, int NS) {
   for (int qb = 0; qb < QB; ++qb) {
     const float m = pair32_max(pair16_max(mraw[qb]));
     const int row = qb * 16 + c16;
-    if (g == 0 && row < a.L) sc.m[(((int64_t)br * a.Hq + h) * a.L + row) * NS + sp] = m;
+    if (g == 0 && row < span.Lr) sc.m[(((int64_t)br * a.Hq + h) * a.L + row) * NS + sp] = m;
   }
 }
 
@@ -782,7 +798,8 @@ __global__ __launch_bounds__(512) void attn_gpv_kernel(AttnArgs a, int NS) {
   const int G = a.Hq / a.Hkv;
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int h = kvh * G + wv, g = lane >> 4, c16 = lane & 15;
-  const GroupSplit gs = group_split(a.P, a.L, sp, NS);
+  const AttnSpan span = attn_span(a, br);
+  const GroupSplit gs = group_split(span.P, span.Lk, sp, NS);
   const int np = gs.np;
   const float sl2 = a.scale * 1.4426950408889634f;
   const uint16_t* kc = a.kcache + (int64_t)kvh * D * a.vld;
@@ -796,15 +813,15 @@ __global__ __launch_bounds__(512) void attn_gpv_kernel(AttnArgs a, int NS) {
     for (int i = 0; i < GQ_RING - 1; ++i)
       group_issue<D, QB, true>(a, gs, i, i, ring, kc, vc, ks, vs, lane);
   u32x4 qf[QB][D / 32];
-  group_q<D, QB>(a, br, h, c16, g, qf);
+  group_q<D, QB>(a, br, span.Lr, h, c16, g, qf);
   const GroupScratch sc = group_scratch(a, NS);
   float m[QB], l[QB];
   f32x4 o[NDB][QB];
 #pragma unroll
   for (int qb = 0; qb < QB; ++qb) {
     const int row = qb * 16 + c16;
-    float mx = 0.f;  // rows past L: zero queries, any finite reference
-    if (row < a.L) {
+    float mx = 0.f;  // rows past the block: zero queries, any finite reference
+    if (row < span.Lr) {
       const float* mp = sc.m + (((int64_t)br * a.Hq + h) * a.L + row) * NS;
       mx = mp[0];
       for (int s2 = 1; s2 < NS; ++s2) mx = max2(mx, mp[s2]);
@@ -824,14 +841,14 @@ __global__ __launch_bounds__(512) void attn_gpv_kernel(AttnArgs a, int NS) {
     tile_fetch<D>(smem + (i % GQ_RING) * T::TILE, lane, x);
     const bool pre = i < np;
     tile_update<D, QB, false>(x, qf, m, l, o, (pre ? gs.p_lo + i : i - np) * KT,
-                              pre ? a.P : a.L, sl2, g, pre ? 0 : a.cblk, 0);
+                              pre ? span.P : span.Lk, sl2, g, pre ? 0 : a.cblk, 0);
   }
   if (wv == 0) attn_wait_vmcnt<0>();
 #pragma unroll
   for (int qb = 0; qb < QB; ++qb) {
     const float ls = pair32_sum(pair16_sum(l[qb]));
     const int row = qb * 16 + c16;
-    if (row >= a.L) continue;
+    if (row >= span.Lr) continue;
     const int64_t r = (((int64_t)sp * a.nb + br) * a.Hq + h) * a.L + row;
     if (g == 0) sc.l[r] = ls;
 #pragma unroll
@@ -845,9 +862,10 @@ __global__ __launch_bounds__(256) void attn_gmerge_kernel(AttnArgs a, int NS) {
   const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int q4 = (int)(t % (D / 4));
   const int64_t rr = t / (D / 4);  // (branch, head, row)
-  const bool ok = rr < (int64_t)a.nb * a.Hq * a.L;
-  const int64_t r = ok ? rr : 0;
+  const bool in = rr < (int64_t)a.nb * a.Hq * a.L;
+  const int64_t r = in ? rr : 0;
   const int row = (int)(r % a.L), h = (int)((r / a.L) % a.Hq), br = (int)(r / ((int64_t)a.L * a.Hq));
+  const bool ok = in && row < attn_span(a, br).Lr;
   const GroupScratch sc = group_scratch(a, NS);
   const int64_t rows = (int64_t)a.nb * a.Hq * a.L;
   f32x4 acc = *(const f32x4*)(sc.o + r * D + q4 * 4);
@@ -897,7 +915,9 @@ hipError_t launch_group(const AttnArgs& a, int NS, hipStream_t s) {
 
 template <int D>
 hipError_t launch_d(const AttnArgs& a, hipStream_t s) {
-  const int T = (a.P + KT - 1) / KT + (a.L + KT - 1) / KT;
+  // the longest span: the last branch's
+  const AttnSpan span = attn_span(a, a.nb - 1);
+  const int T = (span.P + KT - 1) / KT + (span.Lk + KT - 1) / KT;
   const int nt = (T + SL_WAVES - 1) / SL_WAVES;  // most tiles of one wavefront
   if (a.L <= 32 && nt <= 3) {
     if (a.L <= 16) return launch_sl<D, 1>(a, nt, s);
@@ -907,7 +927,7 @@ hipError_t launch_d(const AttnArgs& a, hipStream_t s) {
   if (a.L <= 32 && G >= 2 && G <= 8 && a.scratch) {
     // key splits: enough workgroups for the chip, at least 4 prefix tiles each,
     // within the scratch
-    const int pt = (a.P + KT - 1) / KT;
+    const int pt = (span.P + KT - 1) / KT;
     int NS = group_splits(a.nb, a.Hkv);
     NS = std::min(NS, std::max(1, pt / 4));
     while (NS > 1 && group_scratch_floats(a, NS) * 4 > a.scratch_bytes) --NS;
@@ -938,6 +958,9 @@ size_t attention_scratch_bytes(int nb, int L, int Hq, int Hkv, int d) {
 hipError_t launch_attention(const AttnArgs& a, hipStream_t s) {
   if (a.L < 1 || a.L > 256 || a.P < 0 || a.Hq % a.Hkv || a.vld % KT || a.vlds % KT ||
       a.L > a.vlds || a.P > a.vld)
+    return hipErrorInvalidValue;
+  if (a.chain_rows && (a.cblk || a.chain_rows <= (a.nb - 1) * a.L || a.chain_rows > a.nb * a.L ||
+                       a.P + a.chain_rows > a.vld))
     return hipErrorInvalidValue;
   if (a.cblk < 0 || (a.cblk > 0 && (a.cblk % 16 || a.L % a.cblk))) return hipErrorInvalidValue;
   if (a.d == 128) return launch_d<128>(a, s);

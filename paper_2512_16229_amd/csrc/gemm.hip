@@ -630,7 +630,8 @@ __global__ __launch_bounds__(256) void gemm_fixup_kernel(GemmArgs a) {
     // a block may be shorter than four rows
     br[j] = j == 0 ? br0 : pos[j - 1] + 1 == a.L ? br[j - 1] + 1 : br[j - 1];
     pos[j] = j == 0 ? pos0 : pos[j - 1] + 1 == a.L ? 0 : pos[j - 1] + 1;
-    cs[j] = rot ? *(const float2*)(a.rope + ((int64_t)(a.P + pos[j]) * HD + dim) * 2)
+    const int at = a.P + (!a.chain ? pos[j] : r0 + j < a.M ? r0 + j : 0);  // position of the row
+    cs[j] = rot ? *(const float2*)(a.rope + ((int64_t)at * HD + dim) * 2)
                 : make_float2(1.f, 0.f);
     sr[j] = a.f8 && r0 + j < a.M ? a.sa[r0 + j] : 0.f;
   }
@@ -659,15 +660,20 @@ __global__ __launch_bounds__(256) void gemm_fixup_kernel(GemmArgs a) {
       qo[dim] = f2bf_bits(o1);
       qo[dim + HD] = f2bf_bits(o2);
     } else {
-      // staging head (K or V) of this branch and layer, in the KV tile layout
-      uint16_t* st = a.staging + ((((int64_t)br[j] * a.layers + a.layer) * 2 + (sect - 1)) *
-                                      a.Hkv + head) * D * a.vlds;
-      if (sect == 1) {
-        st[kv_k_off(i, dim, D)] = f2bf_bits(o1);
-        st[kv_k_off(i, dim + HD, D)] = f2bf_bits(o2);
-      } else {
-        st[kv_v_off(i, dim, D)] = f2bf_bits(o1);
-      }
+      // K or V of this head, in the KV tile layout: position i of a region
+      auto put = [&](uint16_t* st, int i) {
+        if (sect == 1) {
+          st[kv_k_off(i, dim, D)] = f2bf_bits(o1);
+          st[kv_k_off(i, dim + HD, D)] = f2bf_bits(o2);
+        } else {
+          st[kv_v_off(i, dim, D)] = f2bf_bits(o1);
+        }
+      };
+      if (a.chain)
+        put((sect == 1 ? a.kcache : a.vcache) + (int64_t)head * D * a.vld, a.P + r0 + j);
+      if (!a.chain || br[j] == a.stage_block)  // staging of this branch and layer
+        put(a.staging + ((((int64_t)(a.chain ? 0 : br[j]) * a.layers + a.layer) * 2 + (sect - 1)) *
+                             a.Hkv + head) * D * a.vlds, i);
     }
   }
 }

@@ -137,6 +137,11 @@ struct GemmArgs {
   uint16_t* staging;   // [nb][layers][2][Hkv][d * vlds] (the KV tile layout)
   int layer, layers, Hq, Hkv, d, L, P;
   int vlds;            // staging V leading dimension
+  // chain: row r is position P + r of one sequence and its K / V go to the layer's
+  // cache (kcache, vcache: heads d * vld apart); block `stage_block` (rows of
+  // index r / L) also goes to staging branch 0 (-1: none)
+  int chain, stage_block, vld;
+  uint16_t *kcache, *vcache;
   // EPI_RESID
   float* x;            // [M][N] fp32 residual stream (row stride N)
   // EPI_SWIGLU
@@ -171,6 +176,11 @@ struct AttnArgs {
   const uint16_t* staging; // [nb][layers][2][Hkv][d * vlds]
   uint16_t* out;           // packed activations (Mp rows, Hq*d columns)
   int nb, L, P, Hq, Hkv, d, vld, layer, layers, vlds, Mp;
+  // > 0: the nb branches are consecutive blocks of L rows of one sequence,
+  // chain_rows rows in all (the last block may be short), whose K / V already lie
+  // in the cache from position P on: block b sees the cache up to its own end,
+  // the staging is not read. 0: independent branches.
+  int chain_rows;
   float scale;
   // block-causal mask inside the block (cblk > 0, a multiple of 16 dividing L):
   // a row of sub-block r / cblk sees the prefix and the block keys of the

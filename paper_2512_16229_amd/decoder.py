@@ -4,7 +4,7 @@ One iteration (Alg. 1) = build_branches -> verify_forward (all k+1 branches in
 one pass) -> branch_confidence_select -> commit_kv, all enqueued on one
 stream; the only host read per iteration is the winner's unfilled count (a
 4-byte copy) that ends the block. Prompt encoding is block-causal in blocks of
-L through the same verify forward with one branch, committed block by block.
+L, runs of blocks at a time (lopa_prefill).
 """
 from __future__ import annotations
 
@@ -12,7 +12,7 @@ import torch
 
 from . import (KV, MAX_BLOCK, METRIC_MEAN, WINDOW_MAX_BLOCKS, Model,
                lopa_branch_confidence_select, lopa_branch_confidence_select_metric,
-               lopa_build_branches, lopa_build_branches_window, lopa_commit_kv,
+               lopa_build_branches, lopa_build_branches_window, lopa_commit_kv, lopa_prefill,
                lopa_verify_forward, lopa_window_commit, lopa_window_init, lopa_window_update,
                window_read, window_state)
 
@@ -53,6 +53,12 @@ class Decoder:
     def prefill(self, prompt: torch.Tensor) -> int:
         """Encode the prompt block-causally; returns the new prefix length."""
         prompt = prompt.to(device="cuda", dtype=torch.int32).contiguous()
+        n = prompt.numel()
+        if n and not 0 < self.kv.block_causal < min(self.L, n):
+            lopa_prefill(self.model, self.kv, 0, prompt, self.L)
+            self.append_offset.fill_((n - 1) // self.L * self.L)  # the last block's
+            return n
+        # a mask inside the blocks: block by block through the verify forward
         pos = 0
         conf = torch.empty(self.L, dtype=torch.float32, device="cuda")
         pred = torch.empty(self.L, dtype=torch.int32, device="cuda")

@@ -28,6 +28,61 @@ def _d(a, dt):
     return torch.tensor(np.asarray(a), dtype=dt, device="cuda").contiguous()
 
 
+# (config, tokens, block, branches, precision): a short last block, one block, a
+# block longer than the prompt, runs that end at and inside a run of the working
+# buffers (256 rows, 8 x 64), one-row blocks, head_dim 128, each attention form
+# (single-load, grouped past 24 key tiles, 64-row blocks, MHA-like 2:1)
+PREFILL = [("small", 37, 32, 1, "bf16"), ("small", 32, 32, 8, "bf16"), ("small", 20, 32, 2, "bf16"),
+           ("small", 256, 32, 1, "fp8"), ("small", 263, 7, 1, "bf16"), ("tiny", 9, 1, 1, "bf16"),
+           ("small128", 1000, 32, 8, "bf16"), ("small", 900, 16, 1, "fp8"),
+           ("small128", 530, 64, 8, "bf16"), ("tiny", 700, 50, 3, "fp8_mlp")]
+
+
+@pytest.mark.parametrize("cfgname,n,L,nb,prec", PREFILL)
+def test_prefill_runs_equal_block_by_block(cfgname, n, L, nb, prec):
+    """lopa_prefill (runs of blocks through the layers together) against the
+    verify forward and commit of block after block: the same cache up to the
+    rounding of another split of the same sums, and the same state after it."""
+    import paper_2512_16229_amd as lp
+    from gpu_util import LAYER_TOL, LAYER_TOL_FP8, rel_l2, to_dev_bf16
+    log(f"prefill {cfgname} {n} tokens in blocks of {L}, {nb} branches, {prec}")
+    cfg = synth.config(cfgname)
+    model = lp.Model(cfg, to_dev_bf16(synth.model_weights(cfg)), precision=prec)
+    tokens = synth.prompt(cfg, n).to(device="cuda", dtype=I32)
+    kv, ref = (lp.KV(model, n + 3, nb, L) for _ in range(2))
+    off, zero = torch.empty(1, dtype=I32, device="cuda"), torch.zeros(1, dtype=I32, device="cuda")
+    conf, pred = (torch.empty(L, dtype=t, device="cuda") for t in (F32, I32))
+    pre = min(3, n - 1)  # the first tokens as a block of their own: a prefix of any length
+    pos = 0
+    while pos < n:
+        m = min(L, n - pos) if pos else min(pre, L) or min(L, n)
+        lp.lopa_verify_forward(model, ref, pos, tokens[pos:pos + m], 1, m, conf[:m], pred[:m])
+        lp.lopa_commit_kv(ref, zero, pos, m, off)
+        if pos + m == n:
+            break
+        pos += m
+    if 0 < pre <= L:
+        lp.lopa_prefill(model, kv, 0, tokens[:pre], L)
+        lp.lopa_prefill(model, kv, pre, tokens[pre:], L)
+    else:
+        lp.lopa_prefill(model, kv, 0, tokens, L)
+    tol = LAYER_TOL if prec == "bf16" else LAYER_TOL_FP8
+    for layer in range(cfg["layers"]):
+        for a, b in zip(kv.read(layer, 0, n), ref.read(layer, 0, n)):
+            assert rel_l2(a.float().cpu().numpy(), b.float().cpu().numpy()) < tol
+        # the last block's rows are staged, as after its forward
+        for a, b in zip(kv.read_staging(0, layer, m), kv.read(layer, pos, m)):
+            assert torch.equal(a, b)
+    lp.lopa_commit_kv(kv, zero, pos, m, off)  # the handle's state too
+    assert int(off.item()) == pos
+    for bad, code in ((dict(block=0), -2), (dict(prefix=4), -3), (dict(block=L + 1), -2)):
+        if "block" in bad and bad["block"] > n:
+            continue
+        with pytest.raises(lp.LopaError) as e:
+            lp.lopa_prefill(model, kv, bad.get("prefix", 0), tokens, bad.get("block", L))
+        assert e.value.status == code
+
+
 @pytest.mark.parametrize("cfgname,P,L,k,tau", [("tiny", 64, 16, 3, 0.9), ("tiny", 64, 16, 7, 0.5),
                                                ("small", 100, 32, 7, 0.9), ("tiny", 40, 16, 3, 0.999)])
 def test_teacher_forced_iterations(cfgname, P, L, k, tau):
