@@ -436,13 +436,15 @@ __global__ __launch_bounds__(256) void attn_kernel(AttnArgs a) {
 
 // ---------------------------------------------------------------------------
 // Single-load form, for key ranges short enough that every score of the
-// workgroup fits in registers (at most SL_WAVES x NT tiles). Eight wavefronts
-// split the key tiles; each loads its tiles' K straight into registers in
-// MFMA operand layout, forms and keeps the scores, then loads V into the same
-// registers while the row maxima are exchanged through LDS. The probabilities
-// are formed once, against the exact maximum, from the kept scores, so K and V
-// cross the memory system once and the path has two memory round trips
-// instead of one per tile.
+// workgroup fits in registers (SL_WAVES x 8 tiles for a group of 32 query rows,
+// SL_WAVES x 16 for one of 16). Eight wavefronts split the key tiles; each loads
+// its tiles' K straight into registers in MFMA operand layout, forms and keeps
+// the scores, then loads V into registers while the row maxima are exchanged
+// through LDS. The probabilities are formed once, against the exact maximum, from
+// the kept scores, so K and V cross the memory system once, no wavefront waits
+// for another's tile and nothing goes through LDS but the maxima and the final
+// merge. What bounds it is that chain's latency up to one group per CU (10 us at
+// prefix 500, 17 at 1900), then the K / V bytes from L2.
 //
 // In the KV tile layout every K and V fragment a lane needs is its 16 bytes
 // of one contiguous 1 KiB run: the loads are fully coalesced, and the scores
@@ -454,6 +456,7 @@ template <int D, int QB, int NT>
 struct SlSmem {
   static constexpr int NDB = D / 16;
   static constexpr int OV = NDB * QB * 64;  // f32x4 partial-output values of one wavefront
+  static constexpr int BUF = NT <= 3 ? NT : 2;  // K (then V) tiles in flight
 };
 
 template <int D, int QB, int NT>
@@ -464,6 +467,7 @@ __global__ __launch_bounds__(64 * SL_WAVES) void attn_sl_kernel(AttnArgs a) {
   __shared__ float s_max[SL_WAVES][QB * 16];
   __shared__ float s_l[SL_WAVES][QB * 16];
   const int h = blockIdx.x, br = blockIdx.y;
+  const int row0 = blockIdx.z * QB * 16;  // first query row of this workgroup's group
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 4, c16 = lane & 15;
@@ -471,7 +475,8 @@ __global__ __launch_bounds__(64 * SL_WAVES) void attn_sl_kernel(AttnArgs a) {
   const AttnSpan span = attn_span(a, br);
   const int L = a.L, P = span.P, Lk = span.Lk, Lr = span.Lr;
   const int pt = (P + KT - 1) / KT, bt = (Lk + KT - 1) / KT, T = pt + bt;
-  const int t_lo = wv * T / SL_WAVES, nt = (wv + 1) * T / SL_WAVES - t_lo;  // nt <= NT
+  // this wavefront's tiles: t_lo .. t_lo + nt - 1 (nt <= NT)
+  const int t_lo = wv * T / SL_WAVES, nt = (wv + 1) * T / SL_WAVES - t_lo;
   const float sl2 = a.scale * 1.4426950408889634f;
 
   const uint16_t* kc = a.kcache + (int64_t)kvh * D * a.vld;  // KV tile layout
@@ -480,73 +485,98 @@ __global__ __launch_bounds__(64 * SL_WAVES) void attn_sl_kernel(AttnArgs a) {
   const uint16_t* ks = a.staging + (st_base + 0 * a.Hkv + kvh) * D * a.vlds;
   const uint16_t* vs = a.staging + (st_base + 1 * a.Hkv + kvh) * D * a.vlds;
 
-  // K of the wavefront's tiles (whole tiles; keys past a source's end are
-  // masked below)
-  u32x4 kv[NT][2][NKK];
-#pragma unroll
-  for (int i = 0; i < NT; ++i) {
-    if (i >= nt) break;
-    const int t = t_lo + i;
+  // K, then V, of the wavefront's tiles (whole tiles; keys past a source's end
+  // are masked below): BUF tiles in flight, tile i in buffer i % BUF. Up to
+  // three tiles are all in flight at once; with more, two, each refilled when it
+  // has been used (the last tile again past the end, so that no load sits under
+  // a branch).
+  constexpr int BUF = SM::BUF;
+  struct Tile {
+    const uint16_t *k, *v;
+    int p0, lim;  // first key position in its source, the source's end
+    bool pre;
+  };
+  auto tile = [&](int i) -> Tile {
+    // NT > BUF: every wavefront has tiles (T > 24)
+    const int t = t_lo + (NT == BUF || i < nt ? i : nt - 1);
     const bool pre = t < pt;
-    const uint16_t* kt = (pre ? kc : ks) + (int64_t)(pre ? t : t - pt) * KT * D + lane * 8;
+    const int p0 = (pre ? t : t - pt) * KT;
+    return {(pre ? kc : ks) + (int64_t)p0 * D, (pre ? vc : vs) + (int64_t)p0 * D, p0, pre ? P : Lk, pre};
+  };
+  u32x4 kv[BUF][2][NKK], vf[BUF][NDB];
+  auto load_k = [&](u32x4 (&d)[2][NKK], int i) {
+    const uint16_t* kt = tile(i).k + lane * 8;
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-      for (int kk = 0; kk < NKK; ++kk) kv[i][kb][kk] = *(const u32x4*)(kt + (kb * NKK + kk) * 512);
+      for (int kk = 0; kk < NKK; ++kk) d[kb][kk] = *(const u32x4*)(kt + (kb * NKK + kk) * 512);
+  };
+  auto load_v = [&](u32x4 (&d)[NDB], int i) {
+    const uint16_t* vt = tile(i).v + lane * 8;
+#pragma unroll
+    for (int db = 0; db < NDB; ++db) d[db] = *(const u32x4*)(vt + db * 512);
+  };
+#pragma unroll
+  for (int i = 0; i < BUF; ++i) {
+    if (NT == BUF && i >= nt) break;
+    load_k(kv[i], i);
   }
   // Q^T operand: query column 16 qb + c16, dims 32 kk + 8 g .. +8
   u32x4 qf[QB][NKK];
 #pragma unroll
   for (int qb = 0; qb < QB; ++qb) {
-    const int row = qb * 16 + c16;
+    const int row = row0 + qb * 16 + c16;
     const uint16_t* qrow = a.q + (((int64_t)br * a.Hq + h) * L + (row < Lr ? row : 0)) * D;
     const unsigned keep = row < Lr ? ~0u : 0u;  // rows past the block: zero queries
 #pragma unroll
     for (int kk = 0; kk < NKK; ++kk) qf[qb][kk] = *(const u32x4*)(qrow + kk * 32 + g * 8) & keep;
   }
 
-  // scores S^T = K Q^T, kept: sc[i][qb][kb][j] is key p0 + 8 g + 4 kb + j of
-  // tile i, query 16 qb + c16; masked keys -inf
+  // scores S^T = K Q^T of tile i: out[qb][kb][j] is key p0 + 8 g + 4 kb + j,
+  // query row0 + 16 qb + c16; masked keys -inf
+  auto scores = [&](const u32x4 (&k)[2][NKK], int i, f32x4 (&out)[QB][2]) {
+    const Tile t = tile(i);
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+      int lq = t.lim;  // block-causal: rows row0 + 16 qb .. lie in one sub-block
+      if (!t.pre && a.cblk) lq = min(t.lim, ((row0 + qb * 16) / a.cblk + 1) * a.cblk);
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb) {
+        f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kk = 0; kk < NKK; ++kk) acc = mfma16(k[kb][kk], qf[qb][kk], acc);
+        if (t.p0 + KT > lq) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            acc[j] = t.p0 + 8 * g + 4 * kb + j < lq ? acc[j] : -INFINITY;
+        }
+        out[qb][kb] = acc;
+      }
+    }
+  };
   f32x4 sc[NT][QB][2];
   float mraw[QB];
 #pragma unroll
   for (int qb = 0; qb < QB; ++qb) mraw[qb] = -INFINITY;
 #pragma unroll
   for (int i = 0; i < NT; ++i) {
-    if (i >= nt) break;
-    const int t = t_lo + i;
-    const bool pre = t < pt;
-    const int p0 = (pre ? t : t - pt) * KT, lim = pre ? P : Lk;
+    if (NT <= 8 && i >= nt) break;  // (long loops unroll without breaks only)
+    if (i < nt) {
+      scores(kv[i % BUF], i, sc[i]);
 #pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-      int lq = lim;  // block-causal: rows 16 qb .. lie in one sub-block
-      if (!pre && a.cblk) lq = min(lim, ((qb * 16) / a.cblk + 1) * a.cblk);
+      for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
-      for (int kb = 0; kb < 2; ++kb) {
-        f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int kk = 0; kk < NKK; ++kk) acc = mfma16(kv[i][kb][kk], qf[qb][kk], acc);
-        if (p0 + KT > lq) {
-#pragma unroll
-          for (int j = 0; j < 4; ++j)
-            acc[j] = p0 + 8 * g + 4 * kb + j < lq ? acc[j] : -INFINITY;
-        }
-        sc[i][qb][kb] = acc;
-        mraw[qb] = max2(mraw[qb], max2(max2(acc[0], acc[1]), max2(acc[2], acc[3])));
-      }
+        for (int kb = 0; kb < 2; ++kb)
+          mraw[qb] = max2(mraw[qb], max2(max2(sc[i][qb][kb][0], sc[i][qb][kb][1]),
+                                         max2(sc[i][qb][kb][2], sc[i][qb][kb][3])));
     }
+    if (i + BUF < NT) load_k(kv[i % BUF], i + BUF);
   }
-  // V^T of the same keys (the K registers are free now): lane (c16, g) takes
-  // dims 16 db + c16, keys 8 g .. 8 g + 7
-  u32x4 vf[NT][NDB];
+  // V^T of the same keys: lane (c16, g) takes dims 16 db + c16, keys 8 g .. 8 g + 7
 #pragma unroll
-  for (int i = 0; i < NT; ++i) {
-    if (i >= nt) break;
-    const int t = t_lo + i;
-    const bool pre = t < pt;
-    const uint16_t* vt = (pre ? vc : vs) + (int64_t)(pre ? t : t - pt) * KT * D + lane * 8;
-#pragma unroll
-    for (int db = 0; db < NDB; ++db) vf[i][db] = *(const u32x4*)(vt + db * 512);
+  for (int i = 0; i < BUF; ++i) {
+    if (NT == BUF && i >= nt) break;
+    load_v(vf[i], i);
   }
 
   // the exact row maximum over the eight wavefronts (the V loads stay in
@@ -571,20 +601,16 @@ __global__ __launch_bounds__(64 * SL_WAVES) void attn_sl_kernel(AttnArgs a) {
   }
 
   // probabilities against the exact maximum; V meets them rounded to bf16
-#pragma unroll
-  for (int i = 0; i < NT; ++i) {
-    if (i >= nt) break;
-    const int t = t_lo + i;
-    const bool pre = t < pt;
-    const int p0 = (pre ? t : t - pt) * KT, lim = pre ? P : Lk;
-    if (p0 + KT > lim) {
+  auto attend = [&](u32x4 (&v)[NDB], int i, const f32x4 (&sv)[QB][2]) {
+    const Tile t = tile(i);
+    if (t.p0 + KT > t.lim) {
       // zero V at keys past the end of the source (0 * inf would poison o)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const int pos = p0 + 8 * g + 2 * e;
-        const unsigned mk = (pos < lim ? 0xFFFFu : 0u) | (pos + 1 < lim ? 0xFFFF0000u : 0u);
+        const int pos = t.p0 + 8 * g + 2 * e;
+        const unsigned mk = (pos < t.lim ? 0xFFFFu : 0u) | (pos + 1 < t.lim ? 0xFFFF0000u : 0u);
 #pragma unroll
-        for (int db = 0; db < NDB; ++db) vf[i][db][e] &= mk;
+        for (int db = 0; db < NDB; ++db) v[db][e] &= mk;
       }
     }
 #pragma unroll
@@ -595,14 +621,20 @@ __global__ __launch_bounds__(64 * SL_WAVES) void attn_sl_kernel(AttnArgs a) {
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          const float p = fast_exp2(__builtin_fmaf(sc[i][qb][kb][j], sl2, nm));  // -inf: 0
+          const float p = fast_exp2(__builtin_fmaf(sv[qb][kb][j], sl2, nm));  // -inf: 0
           l[qb] += p;
           pb[kb * 4 + j] = f2bf_bits(p);
         }
       const u32x4 pf = *(const u32x4*)pb;  // keys 8 g .. 8 g + 7
 #pragma unroll
-      for (int db = 0; db < NDB; ++db) o[db][qb] = mfma16(vf[i][db], pf, o[db][qb]);
+      for (int db = 0; db < NDB; ++db) o[db][qb] = mfma16(v[db], pf, o[db][qb]);
     }
+  };
+#pragma unroll
+  for (int i = 0; i < NT; ++i) {
+    if (NT <= 8 && i >= nt) break;
+    if (i < nt) attend(vf[i % BUF], i, sc[i]);
+    if (i + BUF < NT) load_v(vf[i % BUF], i + BUF);
   }
 
   // the eight partial states share the maximum: they add up, in wavefront
@@ -622,7 +654,7 @@ __global__ __launch_bounds__(64 * SL_WAVES) void attn_sl_kernel(AttnArgs a) {
   for (int f = tid; f < SM::OV; f += 64 * SL_WAVES) {
     const int ln = f & 63, qb = (f >> 6) % QB, db = (f >> 6) / QB;
     const int q16 = ln & 15, g4 = ln >> 4;
-    const int row = qb * 16 + q16;
+    const int row = row0 + qb * 16 + q16;
     if (row >= Lr) continue;
     f32x4 acc = s_o[0][f];
     float ls = s_l[0][qb * 16 + q16];
@@ -652,7 +684,7 @@ __global__ __launch_bounds__(64 * SL_WAVES) void attn_sl_kernel(AttnArgs a) {
     if (lane < 16) s_m[wv * 16 + lane] = mrow;
     lds_barrier();
     if (tid < 16 * QB) {
-      const int qb = tid >> 4, row = qb * 16 + (tid & 15);
+      const int qb = tid >> 4, row = row0 + qb * 16 + (tid & 15);
       float m = 0.f;
       for (int w = qb; w < SL_WAVES; w += QB) m = fmaxf(m, s_m[w * 16 + (tid & 15)]);
       if (row < Lr) atomicMax(a.rowmax + br * L + row, __float_as_uint(m));
@@ -660,15 +692,29 @@ __global__ __launch_bounds__(64 * SL_WAVES) void attn_sl_kernel(AttnArgs a) {
   }
 }
 
-template <int D, int QB>
-hipError_t launch_sl(const AttnArgs& a, int nt, hipStream_t s) {
-  const dim3 grid(a.Hq, a.nb), block(64 * SL_WAVES);
+// nt: most tiles of one wavefront, at most 8 in 32-row groups, 16 in 16-row groups
+template <int D>
+hipError_t launch_sl(const AttnArgs& a, int nt, int group_rows, hipStream_t s) {
+  const dim3 grid(a.Hq, a.nb, (a.L + group_rows - 1) / group_rows), block(64 * SL_WAVES);
+#define SL(QB, NT) hipLaunchKernelGGL((attn_sl_kernel<D, QB, NT>), grid, block, 0, s, a)
+#define SL12(NT) case NT: if (group_rows == 32) SL(2, NT); else SL(1, NT); break
   switch (nt) {
-    case 1: hipLaunchKernelGGL((attn_sl_kernel<D, QB, 1>), grid, block, 0, s, a); break;
-    case 2: hipLaunchKernelGGL((attn_sl_kernel<D, QB, 2>), grid, block, 0, s, a); break;
-    case 3: hipLaunchKernelGGL((attn_sl_kernel<D, QB, 3>), grid, block, 0, s, a); break;
+    SL12(1);
+    SL12(2);
+    SL12(3);
+    SL12(4);
+    SL12(5);
+    SL12(6);
+    SL12(7);
+    SL12(8);
+    case 9: case 10: SL(1, 10); break;
+    case 11: case 12: SL(1, 12); break;
+    case 13: case 14: SL(1, 14); break;
+    case 15: case 16: SL(1, 16); break;
     default: return hipErrorInvalidValue;
   }
+#undef SL12
+#undef SL
   return hipGetLastError();
 }
 
@@ -919,10 +965,15 @@ hipError_t launch_d(const AttnArgs& a, hipStream_t s) {
   const AttnSpan span = attn_span(a, a.nb - 1);
   const int T = (span.P + KT - 1) / KT + (span.Lk + KT - 1) / KT;
   const int nt = (T + SL_WAVES - 1) / SL_WAVES;  // most tiles of one wavefront
-  if (a.L <= 32 && nt <= 3) {
-    if (a.L <= 16) return launch_sl<D, 1>(a, nt, s);
-    return launch_sl<D, 2>(a, nt, s);
-  }
+  // Single-load form: up to 64 tiles in 32-row groups (us per layer, single-load
+  // against the other forms: Dream-7B 4 x 32 rows at prefix 800 / 1900 12 / 18
+  // against 30 / 33, 16 x 32 rows 23 / 37 against 41 / 54, LLaDA-8B 8 x 32 rows at
+  // 1024 17 against 24, 8 x 256 rows at 1500 103 against 160); up to 128 in 16-row
+  // groups, which read K and V twice as often, while they number less than two
+  // per CU (8 x 32 rows, 448 groups, at 2048 / 3900 34 / 55 against 41 / 55; 16 x 32
+  // rows, 896 groups, 65 / 100 against 54 / 79)
+  if (nt <= 8) return launch_sl<D>(a, nt, a.L <= 16 ? 16 : 32, s);
+  if (nt <= 16 && (int64_t)a.Hq * a.nb * ((a.L + 15) / 16) < 512) return launch_sl<D>(a, nt, 16, s);
   const int G = a.Hq / a.Hkv;
   if (a.L <= 32 && G >= 2 && G <= 8 && a.scratch) {
     // key splits: enough workgroups for the chip, at least 4 prefix tiles each,

@@ -88,6 +88,30 @@ def test_long_prefix_attention(cfgname, P, L, k):
     check_forward(s, bt, conf, pred, label=f"prefix {P}")
 
 
+# the attention forms at their edges: key tiles of 32 (prefix plus block) per
+# wavefront and row groups. 24 / 25 tiles (three in flight, two), 64 / 65 (32-row
+# groups, 16-row groups), 128 / 129 (the other forms), blocks of several 32-row
+# groups with a short last one, a block-causal mask across the groups, and a long
+# prefix with too many 16-row groups for the single-load form
+FORMS = [("tiny", 736, 32, 1, 0), ("tiny", 738, 32, 2, 0), ("small128", 2016, 32, 1, 0),
+         ("small128", 2017, 31, 1, 0), ("tiny", 4032, 64, 1, 0), ("tiny", 4033, 64, 1, 0),
+         ("tiny", 40, 33, 2, 0), ("small128", 70, 200, 1, 0), ("tiny", 500, 96, 1, 48),
+         ("tiny", 2100, 64, 2, 32), ("small", 2100, 64, 15, 0)]
+
+
+@pytest.mark.parametrize("cfgname,P,L,nb,cblk", FORMS)
+def test_attention_forms(cfgname, P, L, nb, cblk):
+    log(f"attention forms {cfgname} P={P} {nb} x {L} mask {cblk}")
+    s = Setup(cfgname, P, L, nb - 1)
+    s.load_oracle_cache()
+    s.kv.set_block_causal(cblk)
+    rng = np.random.default_rng(P + L)
+    mask = s.cfg["mask_id"]
+    bt = np.where(rng.random((nb, L)) < 0.7, mask, rng.integers(0, s.cfg["vocab"] - 1, (nb, L)))
+    conf, pred = s.gpu_forward(bt)
+    check_forward(s, bt, conf, pred, causal_blk=cblk, label=f"P={P} {nb} x {L}")
+
+
 # rows at and around every row tile of the GEMMs (64 mb rows, mb 1..4, and two
 # tiles: 257 rows take 2 x 192, 399 rows 2 x 256), padding rows included
 ROW_TILES = [(1, 64, "bf16"), (5, 13, "bf16"), (2, 64, "fp8"), (3, 43, "fp8"), (3, 64, "bf16"),
