@@ -7,7 +7,8 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_util import f32, log
+import synth
+from gpu_util import f32, log, to_dev_bf16
 from oracle import lopa
 
 pytestmark = pytest.mark.gpu
@@ -152,3 +153,29 @@ def test_commit_copies_only_the_winner(lp):
         s.lp.lopa_verify_forward(s.model, s.kv, 60, torch.zeros(16, dtype=torch.int32, device="cuda"),
                                  1, 16, torch.empty(16, device="cuda"),
                                  torch.empty(16, dtype=torch.int32, device="cuda"))
+
+
+# ranges cut inside the groups of 8 positions and the 32-position tiles, a buffer
+# that is not 16-byte aligned (a view from an odd element), both head dims
+@pytest.mark.parametrize("cfgname", ["tiny", "small128"])
+@pytest.mark.parametrize("start,n,odd", [(0, 1, 0), (0, 64, 0), (3, 9, 0), (7, 1, 1), (8, 40, 1),
+                                         (31, 2, 0), (5, 59, 1), (60, 4, 0)])
+def test_kv_rows_round_trip(cfgname, start, n, odd):
+    import paper_2512_16229_amd as lp
+    cfg = synth.config(cfgname)
+    model = lp.Model(cfg, to_dev_bf16(synth.model_weights(cfg)))
+    kv = lp.KV(model, 64, 1, 8)
+    Hkv, d = cfg["kv_heads"], cfg["head_dim"]
+    g = torch.Generator(device="cuda").manual_seed(start * 64 + n)
+
+    def rows(m):
+        t = torch.empty(Hkv * m * d + 1, dtype=torch.bfloat16, device="cuda")
+        v = t[odd:odd + Hkv * m * d].view(Hkv, m, d)
+        return v.copy_(torch.randn(Hkv, m, d, generator=g, device="cuda"))
+    base, part = (rows(64), rows(64)), (rows(n), rows(n))
+    kv.write(1, 0, *base)
+    kv.write(1, start, *part)
+    for b, p, got, sub in zip(base, part, kv.read(1, 0, 64), kv.read(1, start, n)):
+        want = b.clone()
+        want[:, start:start + n] = p
+        assert torch.equal(got, want) and torch.equal(sub, p)
