@@ -184,23 +184,38 @@ __device__ __forceinline__ void f8_scale(const GemmArgs& a, f32x4 (&acc)[MB][NB]
     }
 }
 
+// One split: the residual add in place. A row block's residual values are all
+// loaded (clamped, no load under a branch) before the first is used: a load per
+// value under its row's test took a memory round trip each (the tiny model's
+// output projection 7.4 us, 4 iterations of it).
 template <int NB, int MB>
 __device__ __forceinline__ void resid_epilogue(const GemmArgs& a, f32x4 (&acc)[MB][NB], int tile,
                                                int row0, int lane) {
   const int g = lane >> 4, c16 = lane & 15;
 #pragma unroll
-  for (int mb = 0; mb < MB; ++mb)
+  for (int mb = 0; mb < MB; ++mb) {
+    float x[4][NB];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int r = row0 + mb * 16 + g * 4 + j;
-      if (r >= a.M) continue;
+      const float* xr = a.x + (int64_t)(r < a.M ? r : a.M - 1) * a.N;
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        const int n = (tile * NB + nb) * 16 + c16;
+        x[j][nb] = xr[n < a.N ? n : a.N - 1];
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int r = row0 + mb * 16 + g * 4 + j;
       float* xr = a.x + (int64_t)r * a.N;
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) {
         const int n = (tile * NB + nb) * 16 + c16;
-        if (n < a.N) xr[n] += acc[mb][nb][j];
+        if (r < a.M && n < a.N) xr[n] = x[j][nb] + acc[mb][nb][j];
       }
     }
+  }
 }
 
 // gate / up blocks alternate (block 2p: gate columns 16p.., block 2p + 1: up);
@@ -292,7 +307,8 @@ __device__ __forceinline__ void swiglu_epilogue(const GemmArgs& a, f32x4 (&acc)[
 // (column < vocab, column != mask token) -> pm / ps / pi [row][tile]. Each lane
 // first reduces its NB columns of each of its 16 rows; the 16 lane partials of
 // a row then meet in LDS (red: this wavefront's 16 MB x 16 x 3 words) and one lane
-// per row merges them in column order (ties: lowest column).
+// per row merges them in column order (ties: lowest column); a row's columns are
+// stored xor'd with the row, so that the lanes read 64 banks, not 4.
 template <int NB, int MB>
 __device__ __forceinline__ void lm_epilogue(const GemmArgs& a, f32x4 (&acc)[MB][NB], int tile,
                                             int row0, int lane, float* red) {
@@ -320,7 +336,8 @@ __device__ __forceinline__ void lm_epilogue(const GemmArgs& a, f32x4 (&acc)[MB][
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) s += __builtin_amdgcn_exp2f((v[nb] - m) * LOG2E);
       if (m == -INFINITY) s = 0.f;
-      const int o = (mb * 16 + g * 4 + j) * 16 + c16;
+      const int row = mb * 16 + g * 4 + j;
+      const int o = row * 16 + (c16 ^ (row & 15));
       rm[o] = m;
       rs[o] = s;
       ri[o] = mi;
@@ -331,7 +348,7 @@ __device__ __forceinline__ void lm_epilogue(const GemmArgs& a, f32x4 (&acc)[MB][
   int I = 0x7fffffff;
 #pragma unroll
   for (int c = 0; c < 16; ++c) {
-    const int o = (lane < ROWS ? lane : 0) * 16 + c;
+    const int o = (lane < ROWS ? lane : 0) * 16 + (c ^ (lane & 15));
     const float mc = rm[o], sc = rs[o];
     const int ic = ri[o];
     if (mc > M) {
