@@ -719,8 +719,8 @@ hipError_t launch_sl(const AttnArgs& a, int nt, int group_rows, hipStream_t s) {
 }
 
 // ---------------------------------------------------------------------------
-// Grouped form, for key ranges too long for the single-load form (more than
-// SL_WAVES x 3 tiles) with grouped-query heads (2..8 query heads per KV head).
+// Grouped form, for blocks of up to 32 rows with key ranges too long for the
+// single-load form (launch_d) and grouped-query heads (2..8 per KV head).
 // The keys are cut into NS splits; a workgroup takes one (KV head, branch,
 // split) with one wavefront per query head of the group, so that every K / V
 // tile crosses into the CU once for all the group's heads (wavefront 0 copies
