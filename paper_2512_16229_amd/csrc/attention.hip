@@ -19,6 +19,7 @@
 // query c16, the order in which the probabilities meet V in O^T = V^T P^T.
 // Keys past the end of a source (the last prefix tile, a block shorter than
 // 32) are masked: their scores are -inf and their V values zero.
+#include "attn_span.h"
 #include "common.h"
 #include "kernels.h"
 
@@ -29,19 +30,8 @@
 
 namespace {
 
-constexpr int KT = 32;  // keys per tile
-
-// What the rows of branch br see: P cache positions, then Lk keys of their own
-// staging; Lr rows. Chained (AttnArgs::chain_rows): branch br is block br of a
-// run of blocks whose K / V are in the cache already, and sees the cache up to
-// its own end; the last block may be short.
-struct AttnSpan {
-  int P, Lk, Lr;
-};
 __host__ __device__ __forceinline__ AttnSpan attn_span(const AttnArgs& a, int br) {
-  if (!a.chain_rows) return {a.P, a.L, a.L};
-  const int r0 = br * a.L, left = a.chain_rows - r0, Lr = left < a.L ? left : a.L;
-  return {a.P + r0 + Lr, 0, Lr};
+  return ::attn_span(a.P, a.L, a.chain_rows, br);
 }
 
 template <int D>
@@ -450,13 +440,11 @@ __global__ __launch_bounds__(256) void attn_kernel(AttnArgs a) {
 // of one contiguous 1 KiB run: the loads are fully coalesced, and the scores
 // of lane (c16, g) are keys 8 g .. 8 g + 7 of the tile, the keys of its V^T
 // fragments.
-constexpr int SL_WAVES = 8;
-
 template <int D, int QB, int NT>
 struct SlSmem {
   static constexpr int NDB = D / 16;
   static constexpr int OV = NDB * QB * 64;  // f32x4 partial-output values of one wavefront
-  static constexpr int BUF = NT <= 3 ? NT : 2;  // K (then V) tiles in flight
+  static constexpr int BUF = sl_buffers(NT);  // K (then V) tiles in flight
 };
 
 template <int D, int QB, int NT>
@@ -474,9 +462,10 @@ __global__ __launch_bounds__(64 * SL_WAVES) void attn_sl_kernel(AttnArgs a) {
   const int kvh = h / (a.Hq / a.Hkv);
   const AttnSpan span = attn_span(a, br);
   const int L = a.L, P = span.P, Lk = span.Lk, Lr = span.Lr;
-  const int pt = (P + KT - 1) / KT, bt = (Lk + KT - 1) / KT, T = pt + bt;
-  // this wavefront's tiles: t_lo .. t_lo + nt - 1 (nt <= NT)
-  const int t_lo = wv * T / SL_WAVES, nt = (wv + 1) * T / SL_WAVES - t_lo;
+  const int pt = prefix_tiles(span), T = key_tiles(span);
+  // this wavefront's tiles: t_lo .. t_lo + nt - 1 (nt <= NT; none where T < 8)
+  const SlRange range = sl_range(T, wv);
+  const int nt = range.nt;
   const float sl2 = a.scale * 1.4426950408889634f;
 
   const uint16_t* kc = a.kcache + (int64_t)kvh * D * a.vld;  // KV tile layout
@@ -487,9 +476,8 @@ __global__ __launch_bounds__(64 * SL_WAVES) void attn_sl_kernel(AttnArgs a) {
 
   // K, then V, of the wavefront's tiles (whole tiles; keys past a source's end
   // are masked below): BUF tiles in flight, tile i in buffer i % BUF. Up to
-  // three tiles are all in flight at once; with more, two, each refilled when it
-  // has been used (the last tile again past the end, so that no load sits under
-  // a branch).
+  // three tiles are all in flight at once (loads under i < nt); with more, two,
+  // each refilled when it has been used, without a branch (sl_tile).
   constexpr int BUF = SM::BUF;
   struct Tile {
     const uint16_t *k, *v;
@@ -497,8 +485,7 @@ __global__ __launch_bounds__(64 * SL_WAVES) void attn_sl_kernel(AttnArgs a) {
     bool pre;
   };
   auto tile = [&](int i) -> Tile {
-    // NT > BUF: every wavefront has tiles (T > 24)
-    const int t = t_lo + (NT == BUF || i < nt ? i : nt - 1);
+    const int t = NT == BUF ? range.t_lo + i : sl_tile(range, i);
     const bool pre = t < pt;
     const int p0 = (pre ? t : t - pt) * KT;
     return {(pre ? kc : ks) + (int64_t)p0 * D, (pre ? vc : vs) + (int64_t)p0 * D, p0, pre ? P : Lk, pre};
@@ -963,7 +950,7 @@ template <int D>
 hipError_t launch_d(const AttnArgs& a, hipStream_t s) {
   // the longest span: the last branch's
   const AttnSpan span = attn_span(a, a.nb - 1);
-  const int T = (span.P + KT - 1) / KT + (span.Lk + KT - 1) / KT;
+  const int T = key_tiles(span);
   const int nt = (T + SL_WAVES - 1) / SL_WAVES;  // most tiles of one wavefront
   // Single-load form: up to 64 tiles in 32-row groups (us per layer, single-load
   // against the other forms: Dream-7B 4 x 32 rows at prefix 800 / 1900 12 / 18

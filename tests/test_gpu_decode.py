@@ -35,7 +35,11 @@ def _d(a, dt):
 PREFILL = [("small", 37, 32, 1, "bf16"), ("small", 32, 32, 8, "bf16"), ("small", 20, 32, 2, "bf16"),
            ("small", 256, 32, 1, "fp8"), ("small", 263, 7, 1, "bf16"), ("tiny", 9, 1, 1, "bf16"),
            ("small128", 1000, 32, 8, "bf16"), ("small", 900, 16, 1, "fp8"),
-           ("small128", 530, 64, 8, "bf16"), ("tiny", 700, 50, 3, "fp8_mlp")]
+           ("small128", 530, 64, 8, "bf16"), ("tiny", 700, 50, 3, "fp8_mlp"),
+           # runs of 800 to 2048 rows: the first blocks see fewer key tiles than a
+           # workgroup has wavefronts, the last see 25 to 64
+           ("small", 1000, 64, 16, "bf16"), ("small128", 900, 32, 25, "bf16"),
+           ("tiny", 2048, 256, 8, "bf16"), ("small", 1100, 64, 16, "fp8")]
 
 
 @pytest.mark.parametrize("cfgname,n,L,nb,prec", PREFILL)
