@@ -414,12 +414,14 @@ int lopa_debug_hidden(const lopa_model* m, lopa_kv* kv, int32_t prefix_len,
  * split-K partial sums, LM-head statistics; the KV cache and staging stay in
  * kv) lives in one device array compiled into the library, of
  * LOPA_NOALLOC_MAX_BYTES per GPU, held by every GPU the library runs on until
- * the process ends. The call allocates nothing and frees nothing; it enqueues
- * a small fill kernel that zeroes the operands' padding columns, then the
- * forward. A shape whose working memory exceeds LOPA_NOALLOC_MAX_BYTES
- * (64 MiB: 256 rows of the Dream-7B or LLaDA-8B shape fit, 512 do not) is
- * LOPA_ESHAPE before anything is enqueued; the current device must be the
- * model's (LOPA_EINVAL). Every call on a GPU shares that GPU's array: calls
+ * the process ends. The call allocates nothing, frees nothing and enqueues the
+ * same kernels with the same bits as lopa_verify_forward where that call's
+ * working memory fits the array (64 MiB: 512 rows of the Dream-7B or LLaDA-8B
+ * shape). Past that it splits the projections' sums less often: the same
+ * products added in another order, so the results agree up to that rounding. A
+ * shape that does not fit then either is LOPA_ESHAPE before anything is
+ * enqueued; the current device must be the model's (LOPA_EINVAL). Every call on
+ * a GPU shares that GPU's array: calls
  * that overlap on one GPU (other streams or threads) race and give undefined
  * results; calls ordered on one stream do not. The first call on a device
  * looks up the array's address there (not inside a capture). */

@@ -15,6 +15,7 @@
 
 #include "../../include/lopa.h"
 #include "kernels.h"
+#include "plan.h"
 #include "verify.h"
 
 namespace {
@@ -78,95 +79,10 @@ struct LayerPack {
   float* ln2;
 };
 
-int round256(int k) { return 256 * ((k + 255) / 256); }
-int round512(int k) { return 512 * ((k + 511) / 512); }
-int round_up(int x, int m) { return m * ((x + m - 1) / m); }
-
-// Row tiles of a forward of M rows: MT = ceil(M / 256) tiles of 64 mb rows each,
-// mb (1..4) the smallest that covers M, so few rows stream few activations.
-struct RowTiles {
-  int MT, mb;
-  int rows() const { return 64 * mb * MT; }
-};
-RowTiles row_tiles(int M) {
-  const int MT = (M + 255) / 256;
-  return {MT, ((M + MT - 1) / MT + 63) / 64};
-}
-// rows of the packed activation buffers of a forward of up to M rows (a smaller
-// forward never takes more: its tiles are as many or fewer, of 256 rows at most)
-int padded_rows(int M) { return 256 * ((M + 255) / 256); }
-
-// Decomposition of one GEMM (see gemm.hip): tile width nb (16-column blocks)
-// and k-splits S; SwiGLU and LM head take no split (their epilogues need whole
-// sums). The pair with the smallest estimated time is taken. A round of
-// workgroups (one per CU) takes the longest of
-//   (a) the bytes one workgroup pulls into its CU, per 64-wide k-chunk the
-//       64 mb x 64 activation chunk from L2 and nb x 2 KiB of weights (61 GB/s),
-//   (b) the round's weight bytes from HBM (7.2 TB/s),
-//   (c) its MFMAs, 5 ns per row block and 32 x 16 weight fragment,
-// plus 0.27 of the shorter of (a) and (c), which overlap in part, plus 0.9 us of
-// fill and tail. Partial sums add their write (5.8 TB/s) and the read of
-// the kernel that adds them (3 TB/s). The constants are a least-squares fit to
-// the GEMM shapes of Dream-7B and LLaDA-8B at 32 to 2048 rows in bf16 and FP8,
-// every (nb, S) of each timed on its own: the plan taken is within 1 % of the
-// best one in the mean, within 17 % in the worst case.
-// max_part: most bytes of partial sums (splits that write more are not taken;
-// QKV keeps one split at least). min_nb: narrowest tile.
-struct GemmPlan {
-  int nb, tiles, splits;
-};
-GemmPlan plan_gemm(int epi, int nblocks, int KC, RowTiles rt, int num_cu,
-                   size_t max_part = SIZE_MAX, int min_nb = 4) {
-  constexpr double CU_BPUS = 61e3, HBM_BPUS = 7.2e6, PART_W_BPUS = 5.8e6, PART_R_BPUS = 3e6;
-  constexpr double FRAG_US = 0.005, OVERLAP = 0.27, FILL_US = 0.9;
-  const bool whole = epi == EPI_SWIGLU || epi == EPI_LMHEAD;
-  const int Q = KC / 4;
-  const int max_s = whole ? 1 : epi == EPI_QKV ? std::min(Q, QKV_MAX_SPLITS) : Q;
-  GemmPlan best{0, 0, 0};
-  double best_t = 1e300;
-  for (int nb : {4, 8, 10}) {
-    if (nb < min_nb || (nb == 10 && !whole)) continue;
-    const int tiles = (nblocks + nb - 1) / nb;
-    for (int S = 1; S <= max_s; ++S) {
-      const int64_t wgs = (int64_t)rt.MT * tiles * S;
-      if (S > 1 && (wgs > 8 * (int64_t)num_cu ||
-                    (size_t)S * rt.rows() * tiles * nb * 16 * 4 > max_part))
-        break;
-      const int64_t rounds = (wgs + num_cu - 1) / num_cu;
-      const double iters = 4.0 * ((Q + S - 1) / S);
-      const double cu = iters * (rt.mb * 8192.0 + nb * 2048.0) / CU_BPUS;
-      const double mfma = iters * rt.mb * nb * 2 * FRAG_US;
-      const double hbm = (double)std::min<int64_t>(wgs, num_cu) / rt.MT * iters * nb * 2048.0 / HBM_BPUS;
-      double t = (double)rounds * (FILL_US + std::max({cu, mfma, hbm}) + OVERLAP * std::min(cu, mfma));
-      if (epi == EPI_QKV || S > 1) {
-        const double part = (double)S * rt.rows() * nblocks * 16 * 4;
-        t += part / PART_W_BPUS + part / PART_R_BPUS;
-      }
-      if (t < best_t) {
-        best_t = t;
-        best = {nb, tiles, S};
-      }
-    }
-  }
-  return best;
-}
-// bytes of fp32 partial sums the plan writes (QKV always goes through them;
-// the residual projections store [splits][rows][N] row-major)
-size_t plan_partial_bytes(int epi, const GemmPlan& p, RowTiles rt, int nblocks) {
-  if (epi == EPI_QKV) return (size_t)rt.rows() * p.tiles * p.nb * 16 * 4 * p.splits;
-  return p.splits > 1 ? (size_t)p.splits * rt.rows() * nblocks * 16 * 4 : 0;
-}
-
 }  // namespace
 
-struct lopa_model {
-  lopa_model_cfg cfg;
+struct lopa_model : ModelShape {
   int device = 0;
-  int num_cu = 0;
-  int n_qkv = 0;
-  int blk_qkv = 0, blk_h = 0, blk_gu = 0, blk_lm = 0;  // packed 16-column blocks
-  int fp8 = 0;       // FP8 MLP (LOPA_PRECISION_FP8_MLP and LOPA_PRECISION_FP8)
-  int fp8_qkv_lm = 0;  // FP8 QKV projection and LM head too (LOPA_PRECISION_FP8)
   std::vector<LayerPack> layers;
   uint16_t* embed = nullptr;
   uint16_t* lm = nullptr;   // bf16 LM head (when not FP8)
@@ -179,17 +95,10 @@ struct lopa_model {
   }
 };
 
-namespace {
-// the row tiles and the plans of the five GEMMs of a verify forward
-struct StepPlans {
-  RowTiles rt;
-  GemmPlan qkv, o, gu, down, lm;
-};
-}  // namespace
-
 struct lopa_kv {
   const lopa_model* m = nullptr;
-  std::vector<StepPlans> plans;  // by row count, up to ws_rows
+  std::vector<StepPlans> plans;  // by row tiles, up to those of ws_rows (plan)
+  const StepPlans& plan(int M) const { return plans[row_tiles(M).index()]; }
   int max_len = 0, max_branches = 0, max_block = 0;
   int ws_rows = 0;              // rows the working buffers hold (plans, qbuf): a forward's
                                 // max_branches * max_block, 256 at least (prompt encoding)
@@ -262,87 +171,6 @@ struct ProfScope {
     if (ev) (void)hipEventRecord(ev->b, s);
   }
 };
-StepPlans plan_step(const lopa_model* m, RowTiles rt, size_t max_part, int min_nb_lm) {
-  const lopa_model_cfg& c = m->cfg;
-  const int kch = m->fp8_qkv_lm ? round512(c.hidden) / 128 : c.hidden / 64;
-  const int kco = m->fp8_qkv_lm ? round512(c.heads * c.head_dim) / 128 : c.heads * c.head_dim / 64;
-  const int kcg = m->fp8 ? round512(c.hidden) / 128 : c.hidden / 64;
-  const int kcd = m->fp8 ? round512(c.ffn) / 128 : round256(c.ffn) / 64;
-  StepPlans p;
-  p.rt = rt;
-  p.qkv = plan_gemm(EPI_QKV, m->blk_qkv, kch, rt, m->num_cu, max_part);
-  p.o = plan_gemm(EPI_RESID, m->blk_h, kco, rt, m->num_cu, max_part);
-  p.gu = plan_gemm(EPI_SWIGLU, m->blk_gu, kcg, rt, m->num_cu);
-  p.down = plan_gemm(EPI_RESID, m->blk_h, kcd, rt, m->num_cu, max_part);
-  p.lm = plan_gemm(EPI_LMHEAD, m->blk_lm, kch, rt, m->num_cu, SIZE_MAX, min_nb_lm);
-  return p;
-}
-// bytes of partial sums and LM-head (row, tile) statistics of a forward
-size_t partial_bytes(const lopa_model* m, const StepPlans& p) {
-  return std::max({(size_t)16, plan_partial_bytes(EPI_QKV, p.qkv, p.rt, m->blk_qkv),
-                   plan_partial_bytes(EPI_RESID, p.o, p.rt, m->blk_h),
-                   plan_partial_bytes(EPI_RESID, p.down, p.rt, m->blk_h)});
-}
-size_t lm_stats(const StepPlans& p) { return (size_t)p.rt.rows() * p.lm.tiles; }
-
-// The regions of a forward's working memory, in carving order (bytes, each
-// rounded up to 256): x, abuf, fbuf, qbuf, partials, pm, ps, pi, then the FP8
-// operands of FP8 models. M rows; scratch: the attention's.
-struct WsLayout {
-  size_t sz[13] = {};
-  size_t total() const {
-    size_t t = 0;
-    for (size_t v : sz) t += v;
-    return t;
-  }
-};
-WsLayout ws_layout(const lopa_model* m, const StepPlans& p, int M, size_t scratch) {
-  const lopa_model_cfg& c = m->cfg;
-  const size_t rows = p.rt.rows();
-  WsLayout w;
-  w.sz[0] = rows * c.hidden * 4;
-  w.sz[1] = rows * c.hidden * 2;
-  w.sz[2] = rows * round256(c.ffn) * 2;
-  w.sz[3] = (size_t)M * c.heads * c.head_dim * 2;
-  w.sz[4] = std::max(partial_bytes(m, p), scratch);
-  w.sz[5] = w.sz[6] = w.sz[7] = lm_stats(p) * 4;
-  if (m->fp8) {
-    w.sz[8] = rows * round512(c.hidden);
-    w.sz[9] = rows * round512(c.ffn);
-    w.sz[10] = w.sz[11] = w.sz[12] = rows * 4;
-  }
-  for (size_t& v : w.sz) v = (v + 255) / 256 * 256;
-  return w;
-}
-// Both entries of the verify forward take the same plans (the same bits), so a
-// forward whose other buffers fit the static array of lopa_verify_forward_noalloc
-// takes only as many splits, and as narrow an LM-head tile, as let all of it fit.
-// free_plan: plan_step of the same row tiles without a limit.
-StepPlans fit_plan(const lopa_model* m, int M, const StepPlans& free_plan) {
-  constexpr size_t CAP = (size_t)LOPA_NOALLOC_MAX_BYTES;
-  const WsLayout w = ws_layout(m, free_plan, M, 0);
-  const size_t stats = w.sz[5] + w.sz[6] + w.sz[7];
-  if (w.total() <= CAP || w.total() - w.sz[4] - stats >= CAP) return free_plan;
-  StepPlans p = plan_step(m, free_plan.rt, SIZE_MAX, 8);
-  const WsLayout w8 = ws_layout(m, p, M, 0);
-  if (w8.total() <= CAP) return p;
-  const size_t rest = w8.total() - w8.sz[4];
-  if (rest >= CAP) return free_plan;
-  p = plan_step(m, free_plan.rt, (CAP - rest) / 256 * 256, 8);
-  return ws_layout(m, p, M, 0).total() <= CAP ? p : free_plan;
-}
-// the plans of every row count up to max_rows (index M; entry 0 unused)
-std::vector<StepPlans> all_plans(const lopa_model* m, int max_rows) {
-  std::vector<StepPlans> v((size_t)max_rows + 1);
-  StepPlans free_plan{};
-  for (int M = 1; M <= max_rows; ++M) {
-    const RowTiles rt = row_tiles(M);
-    if (M == 1 || rt.MT != free_plan.rt.MT || rt.mb != free_plan.rt.mb)
-      free_plan = plan_step(m, rt, SIZE_MAX, 4);
-    v[M] = fit_plan(m, M, free_plan);
-  }
-  return v;
-}
 }  // namespace
 
 extern "C" {
@@ -407,14 +235,9 @@ int lopa_model_create_ex(const lopa_model_cfg* cfg, const lopa_weight_ptrs* w, i
   }
   hipStream_t s = (hipStream_t)stream;
   lopa_model* m = new lopa_model();
-  m->cfg = *cfg;
+  m->set(*cfg, precision);
   const lopa_model_cfg& c = *cfg;
   const int H = c.hidden, d = c.head_dim, F = c.ffn, V = c.vocab;
-  m->n_qkv = (c.heads + 2 * c.kv_heads) * d;
-  m->blk_qkv = m->n_qkv / 16;
-  m->blk_h = H / 16;
-  m->blk_gu = 2 * F / 16;
-  m->blk_lm = (V + 15) / 16;
   auto bail = [&](int code) {
     delete m;
     return code;
@@ -423,8 +246,6 @@ int lopa_model_create_ex(const lopa_model_cfg* cfg, const lopa_weight_ptrs* w, i
       hipDeviceGetAttribute(&m->num_cu, hipDeviceAttributeMultiprocessorCount, m->device) !=
           hipSuccess)
     return bail(fail(LOPA_EHIP, "no HIP device"));
-  m->fp8 = precision == LOPA_PRECISION_FP8_MLP || precision == LOPA_PRECISION_FP8;
-  m->fp8_qkv_lm = precision == LOPA_PRECISION_FP8;
   auto alloc16 = [&](uint16_t** p, size_t elems) -> int {
     DevBuf b;
     int r = dalloc(b, elems * 2, m->owned);
@@ -594,8 +415,7 @@ int lopa_kv_create(const lopa_model* m, int32_t max_len, int32_t max_branches, i
   size_t part_b = 16;
   size_t lm_n = 0;
   kv->plans = all_plans(m, kv->ws_rows);
-  for (int M = 1; M <= kv->ws_rows; ++M) {
-    const StepPlans& p = kv->plans[M];
+  for (const StepPlans& p : kv->plans) {
     part_b = std::max(part_b, partial_bytes(m, p));
     lm_n = std::max(lm_n, lm_stats(p));
   }
@@ -694,7 +514,7 @@ static int verify_impl(const lopa_model* m, lopa_kv* kv, int32_t prefix_len,
   hipStream_t s = (hipStream_t)stream;
   const int M = chain_rows ? chain_rows : n_branches * L;
   const int H = c.hidden, F = c.ffn, d = c.head_dim;
-  const StepPlans& plan = kv->plans[M];
+  const StepPlans& plan = ws.plan;
   const int Mp = plan.rt.rows();
 
   GemmArgs g{};
@@ -905,9 +725,11 @@ static int check_verify(const lopa_model* m, lopa_kv* kv, int32_t prefix_len,
   return LOPA_OK;
 }
 
-// the working buffers the KV handle owns (allocated by lopa_kv_create)
-static VerifyWs kv_ws(const lopa_kv* kv) {
+// the working buffers the KV handle owns (allocated by lopa_kv_create), with the
+// plan of M rows
+static VerifyWs kv_ws(const lopa_kv* kv, int M) {
   VerifyWs w;
+  w.plan = kv->plan(M);
   w.x = kv->x;
   w.abuf = kv->abuf;
   w.fbuf = kv->fbuf;
@@ -931,7 +753,7 @@ int lopa_verify_forward(const lopa_model* m, lopa_kv* kv, int32_t prefix_len,
   int rc = verify_check(m, kv, prefix_len, branch_tokens, n_branches, L, conf, pred);
   if (rc) return rc;
   return verify_impl(m, kv, prefix_len, branch_tokens, n_branches, L, conf, pred, stream, -1,
-                     nullptr, kv_ws(kv));
+                     nullptr, kv_ws(kv, n_branches * L));
 }
 
 int lopa_prefill(const lopa_model* m, lopa_kv* kv, int32_t prefix_len, const int32_t* tokens,
@@ -955,7 +777,7 @@ int lopa_prefill(const lopa_model* m, lopa_kv* kv, int32_t prefix_len, const int
     const int M = std::min(run, n_tokens - pos), nb = (M + L - 1) / L;
     const bool last = pos + M == n_tokens;
     int rc = verify_impl(m, kv, prefix_len + pos, tokens + pos, nb, L, nullptr, nullptr, stream, -1,
-                         nullptr, kv_ws(kv), M, last);
+                         nullptr, kv_ws(kv, M), M, last);
     if (rc) return rc;
     if (last) {  // as after a forward and commit of the last block alone
       kv->last_nb = 1;
@@ -974,7 +796,7 @@ int lopa_debug_hidden(const lopa_model* m, lopa_kv* kv, int32_t prefix_len,
   if (rc) return rc;
   if (n_layers < 0 || n_layers > m->cfg.layers) return fail(LOPA_EINVAL, "n_layers out of range");
   return verify_impl(m, kv, prefix_len, branch_tokens, n_branches, L, nullptr, nullptr, stream,
-                     n_layers, x_out, kv_ws(kv));
+                     n_layers, x_out, kv_ws(kv, n_branches * L));
 }
 
 int lopa_branch_confidence_select_metric(const int32_t* branch_tokens, const float* conf,
@@ -1193,39 +1015,30 @@ int verify_with_ws(const lopa_model* m, lopa_kv* kv, int32_t prefix_len,
                      nullptr, ws);
 }
 
-static WsLayout call_layout(const lopa_kv* kv, int32_t nb, int32_t L) {
-  const lopa_model_cfg& c = kv->m->cfg;
-  return ws_layout(kv->m, kv->plans[nb * L], nb * L,
-                   attention_scratch_bytes(nb, L, c.heads, c.kv_heads, c.head_dim));
-}
-
-size_t verify_ws_bytes(const lopa_kv* kv, int32_t n_branches, int32_t L) {
-  return call_layout(kv, n_branches, L).total();
-}
-
-VerifyWs verify_ws_carve(const lopa_kv* kv, int32_t n_branches, int32_t L, char* base) {
-  const WsLayout w = call_layout(kv, n_branches, L);
-  char* r[13];
-  for (int i = 0; i < 13; ++i) {
-    r[i] = base;
-    base += w.sz[i];
+size_t verify_ws_carve(const lopa_kv* kv, int32_t n_branches, int32_t L, char* base, VerifyWs* out) {
+  const ModelShape* m = kv->m;
+  const lopa_model_cfg& c = m->cfg;
+  const int M = n_branches * L;
+  const size_t scratch = attention_scratch_bytes(n_branches, L, c.heads, c.kv_heads, c.head_dim);
+  VerifyWs& ws = *out;
+  ws = VerifyWs();
+  ws.plan = fit_plan(m, M, scratch, kv->plan(M), LOPA_NOALLOC_MAX_BYTES);
+  const WsLayout w = ws_layout(m, ws.plan, M, scratch);
+  ws.x = (float*)(base + w.x);
+  ws.abuf = (uint16_t*)(base + w.abuf);
+  ws.fbuf = (uint16_t*)(base + w.fbuf);
+  ws.qbuf = (uint16_t*)(base + w.qbuf);
+  ws.partials = (float*)(base + w.shared);
+  ws.partials_bytes = w.shared_bytes;
+  ws.pm = (float*)(base + w.shared);
+  ws.ps = (float*)(base + w.shared + w.stats_bytes);
+  ws.pi = (int32_t*)(base + w.shared + 2 * w.stats_bytes);
+  if (m->fp8) {
+    ws.a8_gu = (uint8_t*)(base + w.a8_gu);
+    ws.a8_dn = (uint8_t*)(base + w.a8_dn);
+    ws.sa_gu = (float*)(base + w.sa_gu);
+    ws.sa_dn = (float*)(base + w.sa_dn);
+    ws.rowmax_dn = (uint32_t*)(base + w.rowmax_dn);
   }
-  VerifyWs ws;
-  ws.x = (float*)r[0];
-  ws.abuf = (uint16_t*)r[1];
-  ws.fbuf = (uint16_t*)r[2];
-  ws.qbuf = (uint16_t*)r[3];
-  ws.partials = (float*)r[4];
-  ws.partials_bytes = w.sz[4];
-  ws.pm = (float*)r[5];
-  ws.ps = (float*)r[6];
-  ws.pi = (int32_t*)r[7];
-  if (kv->m->fp8) {
-    ws.a8_gu = (uint8_t*)r[8];
-    ws.a8_dn = (uint8_t*)r[9];
-    ws.sa_gu = (float*)r[10];
-    ws.sa_dn = (float*)r[11];
-    ws.rowmax_dn = (uint32_t*)r[12];
-  }
-  return ws;
+  return w.total;
 }

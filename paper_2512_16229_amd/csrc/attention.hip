@@ -923,12 +923,6 @@ __global__ __launch_bounds__(256) void attn_gmerge_kernel(AttnArgs a, int NS) {
   }
 }
 
-// key splits of the grouped form before the per-call caps: enough workgroups
-// for the chip's 256 CUs, at most 16
-int group_splits(int nb, int Hkv) {
-  return std::min(16, std::max(1, (256 + Hkv * nb - 1) / (Hkv * nb)));
-}
-
 template <int D>
 hipError_t launch_group(const AttnArgs& a, int NS, hipStream_t s) {
   const int G = a.Hq / a.Hkv;
@@ -985,13 +979,6 @@ hipError_t launch_d(const AttnArgs& a, hipStream_t s) {
 }
 
 }  // namespace
-
-size_t attention_scratch_bytes(int nb, int L, int Hq, int Hkv, int d) {
-  const int G = Hkv > 0 ? Hq / Hkv : 0;
-  if (L > 32 || G < 2 || G > 8) return 0;
-  const size_t rows = (size_t)nb * Hq * L;
-  return rows * group_splits(nb, Hkv) * (2 + (size_t)d) * 4;
-}
 
 hipError_t launch_attention(const AttnArgs& a, hipStream_t s) {
   if (a.L < 1 || a.L > 256 || a.P < 0 || a.Hq % a.Hkv || a.vld % KT || a.vlds % KT ||

@@ -2,6 +2,9 @@
 // them into tiles: index arithmetic of attention.hip that a host program can
 // compile too, to check every index it yields.
 #pragma once
+#include <stddef.h>
+
+#include <algorithm>
 
 #if defined(__HIPCC__)
 #include <hip/hip_runtime.h>
@@ -47,4 +50,18 @@ ATTN_HD constexpr int sl_buffers(int NT) { return NT <= 3 ? NT : 2; }
 // which may see 25 tiles and more while the first sees one.
 ATTN_HD int sl_tile(const SlRange& r, int i) {
   return r.t_lo + (i < r.nt ? i : r.nt > 0 ? r.nt - 1 : 0);
+}
+
+// Grouped form: key splits before the per-call caps, enough workgroups for the
+// chip's 256 CUs, at most 16
+inline int group_splits(int nb, int Hkv) {
+  return std::min(16, std::max(1, (256 + Hkv * nb - 1) / (Hkv * nb)));
+}
+// bytes of AttnArgs::scratch that let the grouped form run with its full key
+// splits for nb branches of L rows at any prefix (0: the shape never takes it)
+inline size_t attention_scratch_bytes(int nb, int L, int Hq, int Hkv, int d) {
+  const int G = Hkv > 0 ? Hq / Hkv : 0;
+  if (L > 32 || G < 2 || G > 8) return 0;
+  const size_t rows = (size_t)nb * Hq * L;
+  return rows * group_splits(nb, Hkv) * (2 + (size_t)d) * 4;
 }

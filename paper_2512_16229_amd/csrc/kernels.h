@@ -3,6 +3,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "attn_span.h"
+#include "plan.h"
+
 #include "../../include/lopa.h"
 
 // ----------------------------------------------------------- step kernels
@@ -108,9 +111,6 @@ hipError_t launch_lm_merge(const float* pm, const float* ps, const int32_t* pi, 
                            int tiles, float* conf, int32_t* pred, hipStream_t s);
 
 // ---------------------------------------------------------------- GEMM
-enum { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_LMHEAD = 3 };
-// most k-splits of the QKV projection (its fix-up sums them with the count as a constant)
-constexpr int QKV_MAX_SPLITS = 8;
 // widest column tile in 16-column blocks: a packed weight (and its column
 // scales) is followed by this many blocks of slack, which the last tile reads
 constexpr int GEMM_MAX_NB = 10;
@@ -197,6 +197,3 @@ struct AttnArgs {
   uint32_t* rowmax;
 };
 hipError_t launch_attention(const AttnArgs& a, hipStream_t s);
-// bytes of AttnArgs::scratch that let the grouped form run with its full key
-// splits for nb branches of L rows at any prefix (0: the shape never takes it)
-size_t attention_scratch_bytes(int nb, int L, int Hq, int Hkv, int d);

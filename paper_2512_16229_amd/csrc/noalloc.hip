@@ -44,7 +44,8 @@ extern "C" int lopa_verify_forward_noalloc(const lopa_model* m, lopa_kv* kv, int
                                            int32_t L, float* conf, int32_t* pred, void* stream) {
   int rc = verify_check(m, kv, prefix_len, branch_tokens, n_branches, L, conf, pred);
   if (rc) return rc;
-  const size_t need = verify_ws_bytes(kv, n_branches, L);
+  VerifyWs ws;
+  const size_t need = verify_ws_carve(kv, n_branches, L, nullptr, &ws);
   if (need > (size_t)LOPA_NOALLOC_MAX_BYTES)
     return lopa_fail(LOPA_ESHAPE,
                      "lopa_verify_forward_noalloc: %d branches x %d rows need %zu bytes of "
@@ -57,7 +58,7 @@ extern "C" int lopa_verify_forward_noalloc(const lopa_model* m, lopa_kv* kv, int
                      model_device(m));
   void* base = nullptr;
   if ((rc = scratch_on_device(dev, &base))) return rc;
-  const VerifyWs ws = verify_ws_carve(kv, n_branches, L, (char*)base);
+  verify_ws_carve(kv, n_branches, L, (char*)base, &ws);
   // the array keeps the last call's contents: every buffer is written before it
   // is read (the forward's first kernel zeroes the operands' padding columns)
   return verify_with_ws(m, kv, prefix_len, branch_tokens, n_branches, L, conf, pred, stream, ws);

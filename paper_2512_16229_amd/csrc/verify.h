@@ -6,12 +6,14 @@
 #include <stdint.h>
 
 #include "../../include/lopa.h"
+#include "plan.h"
 
 // Device memory one verify forward writes and reads besides its inputs,
 // outputs, the weights and the KV cache / staging: the residual stream, the
 // packed GEMM operands, the attention queries, split-K partial sums, the LM
 // head's per-tile softmax statistics, and the FP8 operands and scales.
 struct VerifyWs {
+  StepPlans plan{};            // the decomposition of this forward's GEMMs
   float* x = nullptr;          // [Mp][H] fp32 residual stream
   uint16_t* abuf = nullptr;    // packed [Mp][H] bf16 operand
   uint16_t* fbuf = nullptr;    // packed [Mp][round256(F)] bf16 operand (padding columns zeroed per call)
@@ -28,10 +30,10 @@ struct VerifyWs {
   uint32_t* rowmax_dn = nullptr;  // [Mp] SwiGLU row maxima (float bits)
 };
 
-// Bytes of a VerifyWs for n_branches x L rows (within the handle's; regions aligned
-// to 256 bytes), and the carving of such a buffer at base.
-size_t verify_ws_bytes(const lopa_kv* kv, int32_t n_branches, int32_t L);
-VerifyWs verify_ws_carve(const lopa_kv* kv, int32_t n_branches, int32_t L, char* base);
+// The working memory of n_branches x L rows (within the handle's) carved from one
+// piece at base, with the plan that fits LOPA_NOALLOC_MAX_BYTES; returns its bytes
+// (base may be null to learn them).
+size_t verify_ws_carve(const lopa_kv* kv, int32_t n_branches, int32_t L, char* base, VerifyWs* out);
 // lopa_verify_forward with the working buffers ws instead of the KV handle's.
 int verify_with_ws(const lopa_model* m, lopa_kv* kv, int32_t prefix_len,
                    const int32_t* branch_tokens, int32_t n_branches, int32_t L, float* conf,

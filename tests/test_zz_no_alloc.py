@@ -67,3 +67,37 @@ def test_noalloc_refuses_a_shape_beyond_its_array():
     c1, p1, _ = _run(lp, lp.lopa_verify_forward_noalloc, model, kv, 0, bt[:2])
     c0, p0, _ = _run(lp, lp.lopa_verify_forward, model, kv, 0, bt[:2])
     assert np.array_equal(c0, c1) and np.array_equal(p0, p1)
+
+
+# One Dream-7B layer at row counts whose working memory lies near the array's size
+# (512 rows: the regions that are never alive together share memory), and 640 rows,
+# which take fewer splits there: the same sums in another order
+@pytest.mark.parametrize("nb,L,precision,same", [(16, 32, "bf16", True), (8, 64, "fp8", True),
+                                                 (4, 128, "fp8_mlp", True), (10, 64, "bf16", False)])
+def test_noalloc_near_its_array_size(nb, L, precision, same):
+    import paper_2512_16229_amd as lp
+    from gpu_util import LAYER_TOL, rel_l2
+    log(f"noalloc dream7b layer {precision}: {nb} branches x {L} rows")
+    cfg = synth.config("dream7b", layers=1, vocab=16384)
+    w = synth.model_weights(cfg, device="cuda", dtype=torch.bfloat16)
+    model = lp.Model(cfg, w, precision=precision)
+    del w
+    P = 40
+    kv = lp.KV(model, P + L, nb, L)
+    assert lp.Decoder(model, kv, L, nb - 1, 0.9).prefill(synth.prompt(cfg, P)) == P
+    rng = np.random.default_rng(nb * L)
+    mask = cfg["mask_id"]
+    bt = np.where(rng.random((nb, L)) < 0.6, mask, rng.integers(0, cfg["vocab"] - 1, (nb, L)))
+    for rows in (bt, bt[:1]):  # then fewer rows over the first call's contents
+        c1, p1, s1 = _run(lp, lp.lopa_verify_forward_noalloc, model, kv, P, rows)
+        c0, p0, s0 = _run(lp, lp.lopa_verify_forward, model, kv, P, rows)
+        if same or len(rows) == 1:
+            assert np.array_equal(c0, c1) and np.array_equal(p0, p1)
+        else:  # bf16 rows after one layer of the same products; conf ~ 1 / vocab
+            assert rel_l2(c1, c0) < LAYER_TOL
+        for (k0, v0), (k1, v1) in zip(s0, s1):
+            if same or len(rows) == 1:
+                assert torch.equal(k0, k1) and torch.equal(v0, v1)
+            else:
+                for a, b in ((k1, k0), (v1, v0)):
+                    assert rel_l2(a.float().cpu().numpy(), b.float().cpu().numpy()) < LAYER_TOL
