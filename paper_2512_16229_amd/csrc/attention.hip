@@ -508,6 +508,14 @@ __global__ __launch_bounds__(64 * SL_WAVES) void attn_sl_kernel(AttnArgs a) {
     if (NT == BUF && i >= nt) break;
     load_k(kv[i], i);
   }
+  // block-causal: rows row0 + 16 qb .. lie in one sub-block, which sees this many
+  // keys of the staging
+  int seen[QB];
+#pragma unroll
+  for (int qb = 0; qb < QB; ++qb) seen[qb] = Lk;
+  if (a.cblk)
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) seen[qb] = min(Lk, ((row0 + qb * 16) / a.cblk + 1) * a.cblk);
   // Q^T operand: query column 16 qb + c16, dims 32 kk + 8 g .. +8
   u32x4 qf[QB][NKK];
 #pragma unroll
@@ -525,8 +533,7 @@ __global__ __launch_bounds__(64 * SL_WAVES) void attn_sl_kernel(AttnArgs a) {
     const Tile t = tile(i);
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
-      int lq = t.lim;  // block-causal: rows row0 + 16 qb .. lie in one sub-block
-      if (!t.pre && a.cblk) lq = min(t.lim, ((row0 + qb * 16) / a.cblk + 1) * a.cblk);
+      const int lq = t.pre ? t.lim : seen[qb];
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb) {
         f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};

@@ -23,10 +23,10 @@ constexpr int SL_WAVES = 8;  // wavefronts of a single-load workgroup
 struct AttnSpan {
   int P, Lk, Lr;
 };
+// (selects, no branch: it stands before a kernel's first load)
 ATTN_HD AttnSpan attn_span(int P, int L, int chain_rows, int br) {
-  if (!chain_rows) return {P, L, L};
-  const int r0 = br * L, left = chain_rows - r0, Lr = left < L ? left : L;
-  return {P + r0 + Lr, 0, Lr};
+  const int r0 = br * L, left = chain_rows - r0, Lr = chain_rows && left < L ? left : L;
+  return {P + (chain_rows ? r0 + Lr : 0), chain_rows ? 0 : L, Lr};
 }
 // tiles of the prefix, and of the prefix and the staging (at least one)
 ATTN_HD int prefix_tiles(const AttnSpan& s) { return (s.P + KT - 1) / KT; }
