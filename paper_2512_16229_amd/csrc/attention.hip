@@ -953,25 +953,37 @@ hipError_t launch_d(const AttnArgs& a, hipStream_t s) {
   const AttnSpan span = attn_span(a, a.nb - 1);
   const int T = key_tiles(span);
   const int nt = (T + SL_WAVES - 1) / SL_WAVES;  // most tiles of one wavefront
+  // Grouped form where it may run: key splits for the chip, at least 4 prefix tiles
+  // each, within the scratch (0: it may not)
+  const int G = a.Hq / a.Hkv;
+  int NS = 0;
+  if (a.L <= 32 && G >= 2 && G <= 8 && a.scratch) {
+    NS = std::min(group_splits(a.nb, a.Hkv), std::max(1, prefix_tiles(span) / 4));
+    while (NS > 1 && group_scratch_floats(a, NS) * 4 > a.scratch_bytes) --NS;
+    if (group_scratch_floats(a, NS) * 4 > a.scratch_bytes) NS = 0;
+  }
   // Single-load form: up to 64 tiles in 32-row groups (us per layer, single-load
   // against the other forms: Dream-7B 4 x 32 rows at prefix 800 / 1900 12 / 18
   // against 30 / 33, 16 x 32 rows 23 / 37 against 41 / 54, LLaDA-8B 8 x 32 rows at
   // 1024 17 against 24, 8 x 256 rows at 1500 103 against 160); up to 128 in 16-row
   // groups, which read K and V twice as often, while they number less than two
   // per CU (8 x 32 rows, 448 groups, at 2048 / 3900 34 / 55 against 41 / 55; 16 x 32
-  // rows, 896 groups, 65 / 100 against 54 / 79)
-  if (nt <= 8) return launch_sl<D>(a, nt, a.L <= 16 ? 16 : 32, s);
-  if (nt <= 16 && (int64_t)a.Hq * a.nb * ((a.L + 15) / 16) < 512) return launch_sl<D>(a, nt, 16, s);
-  const int G = a.Hq / a.Hkv;
-  if (a.L <= 32 && G >= 2 && G <= 8 && a.scratch) {
-    // key splits: enough workgroups for the chip, at least 4 prefix tiles each,
-    // within the scratch
-    const int pt = (span.P + KT - 1) / KT;
-    int NS = group_splits(a.nb, a.Hkv);
-    NS = std::min(NS, std::max(1, pt / 4));
-    while (NS > 1 && group_scratch_floats(a, NS) * 4 > a.scratch_bytes) --NS;
-    if (group_scratch_floats(a, NS) * 4 <= a.scratch_bytes) return launch_group<D>(a, NS, s);
-  }
+  // rows, 896 groups, 65 / 100 against 54 / 79).
+  // Not with many short branches past 24 tiles: its time goes with the rounds of one
+  // group per CU (11 us each at 62 tiles), a query head's rows fill a part of the 16
+  // and the grouped form takes them for all heads at once. Dream-7B, bf16, branches
+  // of 8 rows at prefix 1900, single-load against grouped: 32 branches (4 rounds)
+  // 51 against 44, 40 (5) 61 / 55, 48 (6) 72 / 58, 64 (7) 83 / 70; of 16 rows 40: 62 / 61,
+  // 48: 74 / 63. At 4 rounds only where the grouped form's own rounds are full
+  // (36 branches take two of them: 49 / 54).
+  const int rounds = (int)(((int64_t)a.Hq * a.nb + 255) / 256);  // of blocks of up to 16 rows
+  const bool crowded =
+      NS && nt > 3 && a.L <= 16 &&
+      (rounds >= 6 || (a.L <= 8 && (rounds == 5 || (rounds == 4 && 3 * ((a.Hkv * a.nb * NS + 255) / 256) <= 2 * NS))));
+  if (nt <= 8 && !crowded) return launch_sl<D>(a, nt, a.L <= 16 ? 16 : 32, s);
+  if (nt > 8 && nt <= 16 && (int64_t)a.Hq * a.nb * ((a.L + 15) / 16) < 512)
+    return launch_sl<D>(a, nt, 16, s);
+  if (NS) return launch_group<D>(a, NS, s);
   // up to 64 query rows per workgroup; longer blocks (multi-block windows) in
   // groups of 64 rows, each group reading all of the branch's keys
   const dim3 grid(a.Hq, a.nb, (a.L + 63) / 64);

@@ -96,7 +96,11 @@ def test_long_prefix_attention(cfgname, P, L, k):
 FORMS = [("tiny", 736, 32, 1, 0), ("tiny", 738, 32, 2, 0), ("small128", 2016, 32, 1, 0),
          ("small128", 2017, 31, 1, 0), ("tiny", 4032, 64, 1, 0), ("tiny", 4033, 64, 1, 0),
          ("tiny", 40, 33, 2, 0), ("small128", 70, 200, 1, 0), ("tiny", 500, 96, 1, 48),
-         ("tiny", 2100, 64, 2, 32), ("small", 2100, 64, 15, 0)]
+         ("tiny", 2100, 64, 2, 32), ("small", 2100, 64, 15, 0),
+         # many short branches: the single-load form up to 5 rounds of 256 (head, branch)
+         # groups of 9 to 16 rows, 4 of up to 8, then the grouped form
+         ("small", 740, 9, 160, 0), ("small", 740, 9, 161, 0), ("small", 740, 8, 128, 0),
+         ("small", 740, 8, 129, 0)]
 
 
 @pytest.mark.parametrize("cfgname,P,L,nb,cblk", FORMS)
