@@ -62,9 +62,6 @@ hipError_t launch_repack(const uint16_t* s0, int r0, const uint16_t* s1, int r1,
                          const uint16_t* s2, int r2, int K, int KP, int blocks, int pairs,
                          uint16_t* dst, hipStream_t s);
 hipError_t launch_bf16_to_f32(const uint16_t* src, float* dst, int n, hipStream_t s);
-// bytes [0, bytes) of device memory p set to zero by a kernel (p and bytes
-// multiples of 16)
-hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s);
 
 // ---------------------------------------------------------------- per-row
 // Padding columns of packed operands that the embedding kernel zeroes for its
