@@ -212,10 +212,11 @@ int lopa_verify_forward(const lopa_model* m, lopa_kv* kv, int32_t prefix_len,
  * and V of tokens[n_tokens] go to the cache positions prefix_len ..
  * prefix_len + n_tokens - 1; a token sees the cache up to the end of its own
  * block. The result is that of encoding block after block with
- * lopa_verify_forward (one branch) and lopa_commit_kv, but runs of blocks, as many
- * rows as the lopa_kv's working buffers hold (max_branches * max_block, 256 at
- * least), go through the layers together, and nothing is computed past the last
- * layer's K and V. Afterwards the lopa_kv is as after the last block's forward
+ * lopa_verify_forward (one branch) and lopa_commit_kv up to rounding: runs of
+ * blocks, as many rows as the lopa_kv's working buffers hold (max_branches *
+ * max_block, 256 at least), go through the layers together, so a run's length, and
+ * with it that capacity, sets the order in which sums are added. Nothing is
+ * computed past the last layer's K and V. Afterwards the lopa_kv is as after the last block's forward
  * (its K and V are staging branch 0). LOPA_ESHAPE: a block (the shorter of `block`
  * and n_tokens) exceeds max_block; LOPA_ECAPACITY: prefix_len + n_tokens >
  * max_len; LOPA_EINVAL: a block exceeds the sub-block set by

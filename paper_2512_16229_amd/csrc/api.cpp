@@ -109,16 +109,16 @@ struct lopa_kv {
   float* rope = nullptr;        // [max_len][d/2][2]
   float* x = nullptr;           // [mp_max][H]
   uint16_t* abuf = nullptr;     // packed [mp_max][H]
-  uint16_t* fbuf = nullptr;     // packed [mp_max][round256(F)], padding columns zero
-  // FP8 models: the FP8 operands of gate/up and down (padding columns zero)
-  // and their per-row scales; a8_gu / sa_gu also carry the normed rows into
-  // the QKV projection and the LM head of LOPA_PRECISION_FP8 models
+  uint16_t* fbuf = nullptr;     // packed [mp_max][round256(F)] (VerifyWs)
+  // FP8 models: the FP8 operands of gate/up and down and their per-row scales;
+  // a8_gu / sa_gu also carry the normed rows into the QKV projection and the LM
+  // head of LOPA_PRECISION_FP8 models
   uint8_t* a8_gu = nullptr;     // packed [mp_max][round512(H)] E4M3
   uint8_t* a8_dn = nullptr;     // packed [mp_max][round512(F)] E4M3
   float* sa_gu = nullptr;
   float* sa_dn = nullptr;
   uint32_t* rowmax_dn = nullptr;  // per-row max |SwiGLU output| (float bits)
-  uint16_t* qbuf = nullptr;     // [max_branches][Hq][max_block][d]
+  uint16_t* qbuf = nullptr;     // ws_rows rows: [branch][Hq][L][d] of a forward
   float* partials = nullptr;
   int causal_blk = 0;           // lopa_kv_set_block_causal: 0 full attention in the block
   float* pm = nullptr;

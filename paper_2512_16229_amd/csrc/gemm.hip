@@ -1,5 +1,5 @@
 // Weight-streaming bf16 GEMM for the skinny row counts of the verify step
-// (M = branches x block rows, at most a few hundred) with fused epilogues:
+// (M = branches x block rows, at most 2048) with fused epilogues:
 //   EPI_QKV    bias + rotate-half RoPE on q/k, q -> attention input, k/v -> the
 //              branch K/V staging (the Pre-Write of Sec. 3.4); always in the
 //              fix-up kernel, where a thread sees both RoPE halves of a column
@@ -9,23 +9,25 @@
 //              exp (the logits never reach memory)
 //
 // Work decomposition. The weight is a sequence of 16-column blocks; a column
-// tile is NB consecutive blocks. A workgroup (4 wavefronts, one per 64 rows)
-// covers one 256-row tile, so each weight byte crosses HBM once per row tile,
-// and one (column tile, k-split): with Q quads of k-chunks, split s owns
-// [s Q / S, (s + 1) Q / S). The tile width NB and the split count S are chosen
-// per GEMM on the host:
+// tile is NB consecutive blocks. A workgroup (4 wavefronts) covers one row tile
+// (below), so each weight byte crosses HBM once per row tile, and one (column
+// tile, k-split): with Q quads of k-chunks, split s owns [s Q / S, (s + 1) Q / S).
+// The tile width NB and the split count S are chosen per GEMM on the host
+// (plan.h):
 //   S == 1  whole K in one workgroup, epilogue in place (no partial sums);
 //   S  > 1  fp32 partial sums, added in split order (deterministic): for the
 //           residual projections by the RMSNorm kernel that follows them, for
 //           QKV by gemm_fixup_kernel, which also runs the QKV epilogue (QKV
 //           always takes this path).
 //
-// What bounds it: the weight stream up to 128 rows (gate/up of the Dream-7B
-// shape, 272 MB: 43.6 us at 32 rows, 6.2 TB/s, against 40-42 us of a copy of the
-// same bytes into LDS and nothing else; the 256-row tile alone took 60 us
-// whatever the rows), and at 256 rows and more the card's power: alone the
-// MFMAs of that projection take 36 us and its memory stream 40, together 60-65,
-// with the clock down from 2.3 GHz (memory alone) to 1.5-1.7 GHz.
+// What bounds it: the memory stream (weights from HBM, activations from L2).
+// Without its MFMAs the same kernel takes the same time up to 128 rows (gate/up of
+// the Dream-7B shape, 272 MB, at 32 rows: 42.3 us a workgroup, 6.4 TB/s; with
+// a tile of 256 rows whatever the call's, 60 us a launch) and 0.90 to 0.97 of it in
+// the short projections of 256 and 512 rows; without its loads 0.6 to 0.76. In
+// gate/up and the LM head at 256 rows and more the card lowers the core clock from
+// 2.4 to 1.9-2.1 GHz, which neither half does alone (gate/up at 256 rows 59 us,
+// memory alone 54.5, MFMAs alone 41).
 //
 // Row tiles. A workgroup's tile is 64 MB rows (wavefront w: row blocks w MB ..
 // w MB + MB - 1), MB = 1 .. 4 the fewest that cover the call's rows in

@@ -382,7 +382,7 @@ __global__ __launch_bounds__(256) void window_commit_kernel(
 
 // Positions [start, start + len) of one layer's K and V between the cache
 // side (heads head_stride apart, KV tile layout) and a caller buffer
-// [Hkv][len][d]. One workgroup per (head, K/V).
+// [Hkv][len][d]; blockIdx.x: (head, K/V), blockIdx.y: 256 threads' worth of it.
 // A thread moves 8 positions (an aligned group) x 8 dimensions: 16-byte runs on
 // both sides (K: 8 dimensions of a position, V: 8 positions of a dimension,
 // transposed in registers), so a head's rows are spread over len d / 64 threads.

@@ -11,7 +11,8 @@
 // Device memory one verify forward writes and reads besides its inputs,
 // outputs, the weights and the KV cache / staging: the residual stream, the
 // packed GEMM operands, the attention queries, split-K partial sums, the LM
-// head's per-tile softmax statistics, and the FP8 operands and scales.
+// head's per-tile softmax statistics, and the FP8 operands and scales. Of one
+// carved piece, what is never alive together shares memory (WsLayout, plan.h).
 struct VerifyWs {
   StepPlans plan{};            // the decomposition of this forward's GEMMs
   float* x = nullptr;          // [Mp][H] fp32 residual stream
