@@ -11,7 +11,7 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_util import Setup, check_forward, gpu_residual, log, rel_l2
+from gpu_util import LAYER_TOL_PURE, Setup, check_forward, gpu_residual, log, rel_l2
 
 pytestmark = pytest.mark.gpu
 
@@ -114,6 +114,30 @@ def test_attention_forms(cfgname, P, L, nb, cblk):
     bt = np.where(rng.random((nb, L)) < 0.7, mask, rng.integers(0, s.cfg["vocab"] - 1, (nb, L)))
     conf, pred = s.gpu_forward(bt)
     check_forward(s, bt, conf, pred, causal_blk=cblk, label=f"P={P} {nb} x {L}")
+
+
+# prompts of many blocks: several runs of 256 rows, one of 1024 and of 800 whose
+# blocks see from 1 to 32 key tiles
+PROMPTS = [("tiny", 1500, 32, 7), ("small", 1000, 64, 15), ("small128", 790, 32, 24),
+           ("small", 700, 25, 0)]
+
+
+@pytest.mark.parametrize("cfgname,P,L,k", PROMPTS)
+def test_long_prompt_against_the_oracle(cfgname, P, L, k):
+    """The cache after lopa_prefill against the oracle's block-by-block encoding.
+    A layer's input is within 1e-2 (rel-L2) of the oracle's
+    (test_hidden_states_per_layer); the rounding of both sides' K / V rows to bf16
+    adds 1.7e-3 each: 2e-2 bounds every block's rows."""
+    log(f"prompt of {P} in blocks of {L}, {k + 1} branches, {cfgname}")
+    s = Setup(cfgname, P, L, k)
+    s.gpu_prefill()
+    for layer in range(s.cfg["layers"]):
+        for name, got, ref in zip("KV", s.kv.read(layer, 0, P), (s.cache_f.k, s.cache_f.v)):
+            _kv_close(got, ref[layer, :, :P], f"{name} l{layer}")
+            # block by block too: an error of one block is not averaged away
+            for b in range(0, P, L):
+                g, r = got[:, b:b + L].float().cpu().numpy(), ref[layer, :, b:min(b + L, P)]
+                assert rel_l2(g, r) < LAYER_TOL_PURE, f"{name} l{layer} block at {b}"
 
 
 # rows at and around every row tile of the GEMMs (64 mb rows, mb 1..4, and two
