@@ -975,11 +975,14 @@ hipError_t launch_d(const AttnArgs& a, hipStream_t s) {
   // of 8 rows at prefix 1900, single-load against grouped: 32 branches (4 rounds)
   // 51 against 44, 40 (5) 61 / 55, 48 (6) 72 / 58, 64 (7) 83 / 70; of 16 rows 40: 62 / 61,
   // 48: 74 / 63. At 4 rounds only where the grouped form's own rounds are full
-  // (36 branches take two of them: 49 / 54).
+  // (36 branches take two of them: 49 / 54). With row maxima its merge does more
+  // (8 rows at prefix 740, FP8: 32 branches 28 / 31, 40: 33 / 37, 48: 39 / 39): 6 rounds.
   const int rounds = (int)(((int64_t)a.Hq * a.nb + 255) / 256);  // of blocks of up to 16 rows
+  const int group_rounds = (a.Hkv * a.nb * NS + 255) / 256;
   const bool crowded =
       NS && nt > 3 && a.L <= 16 &&
-      (rounds >= 6 || (a.L <= 8 && (rounds == 5 || (rounds == 4 && 3 * ((a.Hkv * a.nb * NS + 255) / 256) <= 2 * NS))));
+      (rounds >= 6 || (a.L <= 8 && !a.rowmax &&
+                       (rounds == 5 || (rounds == 4 && 3 * group_rounds <= 2 * NS))));
   if (nt <= 8 && !crowded) return launch_sl<D>(a, nt, a.L <= 16 ? 16 : 32, s);
   if (nt > 8 && nt <= 16 && (int64_t)a.Hq * a.nb * ((a.L + 15) / 16) < 512)
     return launch_sl<D>(a, nt, 16, s);

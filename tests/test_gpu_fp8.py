@@ -59,6 +59,18 @@ def test_fp8_forward_parity(cfgname, P, L, k, prec):
     check_forward(s, bt, conf, pred, label=f"{cfgname} P={P}")
 
 
+# with row maxima many short branches keep the single-load form up to 5 rounds of
+# 256 (head, branch) groups (160 branches of 8 heads), then the grouped form
+@pytest.mark.parametrize("nb", [129, 160, 161])
+def test_fp8_many_short_branches(nb):
+    log(f"fp8 forward small P=740 {nb} x 8")
+    s = Setup("small", 740, 8, nb - 1, precision="fp8")
+    s.load_oracle_cache()
+    bt = _tokens(s, nb, 8, nb)
+    conf, pred = s.gpu_forward(bt)
+    check_forward(s, bt, conf, pred, label=f"small P=740 {nb} x 8")
+
+
 def _tie_free_tokens(s, n, seed):
     """n tokens whose first-layer RMSNorm rows have no value at an E4M3 tie.
     With bf16 embeddings and unit norm weights, 448 x_i / max|x| is often
